@@ -1080,6 +1080,7 @@ __device__ __attribute__((noinline)) void defer_chunk(uint32_t* meta, uint32_t* 
 template <int V>
 __global__ __launch_bounds__(kBlock, kFirstWaves<V>) void k_first(PassArgs a) {
   using S = SpongeShape<V>;
+  kb::absorb_phase_begin();
   a.n = pass_count(a);
   // the staging rows only: 40 KiB for the 136- and 144-byte rates, so four
   // workgroups fit on a CU
@@ -1119,10 +1120,12 @@ __global__ __launch_bounds__(kBlock, kFirstWaves<V>) void k_first(PassArgs a) {
   kb::keccak_rounds_0_22(A);
   kb::keccak_round(A, 23);
   if constexpr (V >= kShake128) {
+    kb::keep_here(A);
     if (valid) kb::squeeze_xof<V>(A, a.out + (c * 64u + lane) * a.stride, a.stride);
   } else {
     uint32_t dig[S::kMaxDigestDw];
     take_digest<V>(dig, A, m.var);
+    kb::keep_here(dig);
     if (valid) put_digest<V>(a.out + (c * 64u + lane) * a.stride, dig);
   }
 }

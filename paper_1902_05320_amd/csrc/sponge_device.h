@@ -139,6 +139,7 @@ __device__ __forceinline__ void sponge_hash(Lane (&A)[25], const uint8_t* msg, u
     const bool fin = b + 1u == nb;
     const uint64_t off = b * static_cast<uint64_t>(R);
     const uint32_t rem = fin ? static_cast<uint32_t>(len - off) : static_cast<uint32_t>(R);
+    absorb_phase_begin();
     if (!PF) load_block<V>(bc, msg + off, rem);
     uint32_t w[S::kMaxRateDw];
     stage_block<V>(row, bc, rem, R, fin, w);
@@ -243,6 +244,7 @@ __device__ __forceinline__ void sponge_hash_words(Lane (&A)[25], const uint8_t* 
   for (uint64_t b = 0; b < nb; ++b) {
     const bool fin = b + 1u == nb;
     const uint32_t rem = rem_of(b);
+    absorb_phase_begin();
     if (!PF) words_to_lds<V>(msg + b * static_cast<uint64_t>(R), rem, area);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     uint2 q[RQ];
