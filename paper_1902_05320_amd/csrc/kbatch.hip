@@ -14,8 +14,8 @@
 //   k_second<.., 1> (tiles)  the grid fills the queue and scatters the
 //             deferred messages into bucketed order.
 //   k_second<.., 2> (hashing)  a resident grid: each SIMD's front wave takes
-//             the split range and then the longest items at raised
-//             priority, the other waves the shortest ones.
+//             the split range and then the longest items, the other waves the
+//             shortest ones.
 // Kernel boundaries order each launch's writes before the next one's reads,
 // so no workgroup waits on another or fences.  On a batch with nothing
 // deferred the last three find no work and return.
@@ -69,8 +69,8 @@ enum : int {
   CTL_ITEM_TILES = 2,
   CTL_NDEF_CHUNKS = 3,  // chunks the first pass deferred
   CTL_MAXKEY = 4,       // largest block-count key deferred
-  CTL_PRIO_KEY = 5,     // front waves raise their priority on items of at least this many blocks
   CTL_SPLIT_N = 6,      // bucketed order positions [0, CTL_SPLIT_N) are hashed in the wide split form
+  CTL_PAIR_KEY = 7,     // items of at least this many blocks are hashed in the pair form
   CTL_USEFUL = 8,       // uint64 (words 8, 9): block counts of the deferred messages
   CTL_DPREFIX = 16,     // words 16..24: exclusive prefix of the deferred sub-list lengths
   CTL_WORDS = 64
@@ -82,9 +82,9 @@ enum : uint32_t {
   kSyncCounters = 4
 };
 
-// One flag per SIMD of the chip, indexed from the wave's hardware id
-// (XCC, shader engine, shader array, CU, SIMD); the first wave to claim its
-// SIMD's flag takes queue items from the front.
+// One word per SIMD of the chip, indexed from the wave's hardware id (XCC,
+// shader engine, shader array, CU, SIMD): the waves that have arrived there.
+// The first one takes queue items from the front.
 constexpr uint32_t kSimdSlots = 8 * 8 * 2 * 16 * 4;
 
 // The queue is dealt round-robin into kQueues sub-queues (item t goes to
@@ -127,7 +127,7 @@ enum : uint32_t {
 struct WorkItem {
   uint32_t begin, end;  // positions in order[]
   uint32_t key;         // block-count bucket of the item
-  uint32_t pad;
+  uint32_t pair;        // 1: hashed in the pair form (32 messages per wave at a time)
 };
 
 // Arguments of the two passes of the persistent form (by value).
@@ -144,6 +144,7 @@ struct PassArgs {
   uint32_t* order;      // bucketed order of the deferred messages, n entries
   WorkItem* items;      // queue items, max_items(n) entries
   uint32_t steps;       // permutations per lane in one queue item
+  uint32_t pair_cap;    // past the split tail, at most this many messages go to the pair form all
   uint32_t split_cap;   // most messages the split tail may take (SHA-3 variants)
   // Per block-count class c, packed so that no array is indexed at run time
   // (an indexed member would move the whole argument block to scratch):
@@ -475,15 +476,15 @@ __device__ __forceinline__ void pair_absorb(uint32_t (&a)[25], const uint8_t* ms
 #pragma unroll
   for (int i = 0; i < 25; ++i) a[i] = 0u;
   const int R = rate_of<V>(var);
-  const uint32_t sh = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(msg) & 3u);
   const uint64_t nb = len / static_cast<uint64_t>(R) + 1u;
   pr::HalfDw<V> d;
-  pr::load_halves<V>(d, msg, sh, len, 0, R, h);
+  pr::load_halves<V>(d, msg, len, 0, R, h);
   for (uint64_t b = 0; b < nb; ++b) {
     const uint64_t boff = b * static_cast<uint64_t>(R);
     const bool fin = b + 1 == nb;
-    pr::absorb_halves<V>(a, d, sh, R, fin, fin ? static_cast<uint32_t>(len - boff) : 0u, S::kPadByte, h);
-    if (!fin) pr::load_halves<V>(d, msg, sh, len, boff + R, R, h);
+    kb::absorb_phase_begin();
+    pr::absorb_halves<V>(a, d, R, fin, fin ? static_cast<uint32_t>(len - boff) : 0u, S::kPadByte, h, hi);
+    if (!fin) pr::load_halves<V>(d, msg, len, boff + R, R, h);
     pr::pair_permute(a, hi);
   }
 }
@@ -514,6 +515,32 @@ __device__ __forceinline__ void pair_xof(uint32_t (&a)[25], uint8_t* out, uint64
   }
 }
 
+// One message hashed by a pair of lanes (h, hi as above).
+template <int V>
+__device__ __forceinline__ void pair_hash_one(const uint8_t* data, const uint64_t* offs,
+                                              const uint64_t* lens, const uint8_t* vars, uint64_t i,
+                                              uint8_t* out, uint64_t stride, uint32_t h, uint32_t hi) {
+  namespace pr = kb::pair;
+  const int slot_dw = V == kMixed ? 16 : V >= kShake128 ? 0 : kb::digest_bytes_of(V) / 4;
+  uint32_t a[25];
+  if constexpr (V >= kShake128) {
+    pair_absorb<V>(a, data + offs[i], lens[i], V, h, hi);
+    pair_xof<V>(a, out + i * stride, stride, h, hi);
+    return;
+  }
+  const int var = V == kMixed ? vars[i] : V;
+  uint32_t* o = reinterpret_cast<uint32_t*>(out + i * stride);
+  if (V == kMixed && var > 3) {  // no such variant: the slot is zeroed
+#pragma unroll
+    for (int k = 0; k < 25; ++k) a[k] = 0u;
+    pr::store_halves(o, a, 0, slot_dw, h);
+    return;
+  }
+  pair_absorb<V>(a, data + offs[i], lens[i], var, h, hi);
+  const int dw = V == kMixed ? kb::digest_bytes_rt(var) / 4 : kb::digest_bytes_of(V) / 4;
+  pr::store_halves(o, a, dw, slot_dw, h);
+}
+
 // Pair form: each pair of lanes hashes one message at a time, message
 // order[first + p] (or first + p) for p = state, state + states, ...  One
 // wave per workgroup, as in the other lane-split forms.
@@ -528,31 +555,11 @@ __global__ __launch_bounds__(kPairBlock) void k_pair(const uint8_t* __restrict__
                                                      const uint32_t* __restrict__ order,
                                                      uint64_t first, uint64_t count,
                                                      uint8_t* __restrict__ out, uint64_t stride) {
-  namespace pr = kb::pair;
-  const uint32_t st = threadIdx.x / pr::kPairLanes, h = threadIdx.x % pr::kPairLanes;
+  const uint32_t st = threadIdx.x / kb::pair::kPairLanes, h = threadIdx.x % kb::pair::kPairLanes;
   const uint32_t hi = h ? ~0u : 0u;
   const uint64_t states = static_cast<uint64_t>(gridDim.x) * kPairStates;
-  const int slot_dw = V == kMixed ? 16 : V >= kShake128 ? 0 : kb::digest_bytes_of(V) / 4;
-  for (uint64_t p = static_cast<uint64_t>(blockIdx.x) * kPairStates + st; p < count; p += states) {
-    const uint64_t i = order ? order[first + p] : first + p;
-    uint32_t a[25];
-    if constexpr (V >= kShake128) {
-      pair_absorb<V>(a, data + offs[i], lens[i], V, h, hi);
-      pair_xof<V>(a, out + i * stride, stride, h, hi);
-      continue;
-    }
-    const int var = V == kMixed ? vars[i] : V;
-    uint32_t* o = reinterpret_cast<uint32_t*>(out + i * stride);
-    if (V == kMixed && var > 3) {  // no such variant: the slot is zeroed
-#pragma unroll
-      for (int k = 0; k < 25; ++k) a[k] = 0u;
-      pr::store_halves(o, a, 0, slot_dw, h);
-      continue;
-    }
-    pair_absorb<V>(a, data + offs[i], lens[i], var, h, hi);
-    const int dw = V == kMixed ? kb::digest_bytes_rt(var) / 4 : kb::digest_bytes_of(V) / 4;
-    pr::store_halves(o, a, dw, slot_dw, h);
-  }
+  for (uint64_t p = static_cast<uint64_t>(blockIdx.x) * kPairStates + st; p < count; p += states)
+    pair_hash_one<V>(data, offs, lens, vars, order ? order[first + p] : first + p, out, stride, h, hi);
 }
 
 // Index of the SIMD this wave runs on, from the HW_ID register (SIMD [5:4],
@@ -816,11 +823,12 @@ __device__ uint32_t block_inclusive_scan(uint32_t v, uint32_t* scratch) {
   return r;
 }
 
-// Messages per queue item in a bucket of `key` blocks: 64 lanes times enough
-// messages that one item is about `steps` permutations per lane.
-__device__ __forceinline__ uint32_t item_msgs(uint32_t key, uint32_t steps) {
+// Messages per queue item in a bucket of `key` blocks: a wave's messages (64,
+// or 32 in the pair form) times enough that one item is about `steps`
+// permutations per lane.
+__device__ __forceinline__ uint32_t item_msgs(uint32_t key, uint32_t steps, bool pair) {
   const uint32_t g = key >= steps ? 1u : steps / (key ? key : 1u);
-  return 64u * g;
+  return (pair ? 32u : 64u) * g;
 }
 
 // Block-count class of a bucket: floor(log2(key)), capped at the last class.
@@ -833,6 +841,12 @@ __device__ __forceinline__ uint32_t class_of_key(uint32_t key) {
 __device__ __forceinline__ uint32_t steps_of(const PassArgs& a, uint32_t key) {
   const uint32_t s = static_cast<uint32_t>(a.class_steps >> (8u * class_of_key(key))) & 0xFFu;
   return s ? s : a.steps;
+}
+
+// Whether a bucket's messages past the split range take the pair form (a
+// class whose tile names the threads per state keeps to that).
+__device__ __forceinline__ bool pair_bucket(const PassArgs& a, uint32_t key, uint32_t pair_key) {
+  return key >= pair_key && ((a.class_threads >> (4u * class_of_key(key))) & 0xFu) == 0u;
 }
 
 // Bucket rank r = kKeyBins - 1 - key orders buckets longest first; in the
@@ -849,6 +863,23 @@ constexpr uint32_t kRanksPerThread = kKeyBins / kBlock;
 // batch of a few equal long messages out of the split form: 8 x 64 KiB ran
 // at 11.0 us per block of the chain, now 3.8.)
 constexpr uint32_t kSplitMinKey = 32;
+
+// Past the split range, the pair form (two lanes per message) takes
+//   - every message, if they are at most two pair waves per SIMD (64 K on 1024
+//     SIMDs): there the one-thread form would leave lanes idle and each chain
+//     runs at one thread's speed.  32768 x 4 KiB SHA3-256: 313 us with one
+//     thread per message, 247 with pairs (6.9 us per block of the chain
+//     against 8.9); at 65536 messages 8.6 against 9.6, at 131072 pairs are the
+//     slower form (15.2 against 13.8);
+//   - of a deep batch (two messages per resident lane and more), those of at
+//     least kPairDeepEighths / 8 x the blocks per resident lane: in the time
+//     that takes a wave that shares its SIMD, the whole batch is hashed, so
+//     these chains would end last.  2^20 uneven messages: no pairs 2.45-2.49
+//     ms, from 9/8 2.29, 11/8 2.13, 12/8 2.12, 13/8 2.31.  (A SIMD left to the
+//     one long item instead gained nothing: 2.36.)
+// Between the two (one item or so per wave) one thread per message keeps the
+// waves of a SIMD at two: 100003 x 1001 B SHA3-384 291 us, 320 with pairs.
+constexpr uint64_t kPairDeepEighths = 12;
 // Wide split items per SIMD's front wave.  Two measured against one
 // (interleaved A/B): serving stream p50 5.23-5.25 against 5.17 ms, p99
 // 7.87-7.95 against 7.70-7.78 ms; 4096 x 16 KiB 8.6 against 14.2 us per
@@ -893,7 +924,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   if (ndef_chunks == 0) {  // every chunk was hashed by the first pass
     if (t == 0) {
       ctl[CTL_NITEMS] = ctl[CTL_TILES] = ctl[CTL_ITEM_TILES] = ctl[CTL_SPLIT_N] = 0u;
-      ctl[CTL_PRIO_KEY] = 0xFFFFFFFFu;
+      ctl[CTL_PAIR_KEY] = 0xFFFFFFFFu;
       ctl[CTL_MAXKEY] = ctl[CTL_USEFUL] = ctl[CTL_USEFUL + 1] = 0u;
     }
     return;
@@ -946,7 +977,6 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     ctl[CTL_USEFUL] = static_cast<uint32_t>(useful);
     ctl[CTL_USEFUL + 1] = static_cast<uint32_t>(useful >> 32);
   }
-  const uint64_t avg = useful / (ndef ? ndef : 1u);
   // bucket starts; the split range ends where the keys drop below kmin
   const uint64_t per_lane = 2u * useful / (a.lanes ? a.lanes : 1u);
   uint64_t kmin64 = kSplitMinKey;
@@ -981,13 +1011,18 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   const uint32_t cap =
       split_all == ndef && ndef <= 2u * a.split_cap ? 2u * a.split_cap : a.split_cap;
   const uint32_t split = split_all < cap ? split_all : cap;
+  // which buckets past it take the pair form (see kPairDeepEighths)
+  uint64_t pair64 = kKeyBins;
+  if (ndef >= 2u * a.lanes) pair64 = kPairDeepEighths * useful / (8u * (a.lanes ? a.lanes : 1u)) + 1u;
+  if (ndef - split <= a.pair_cap) pair64 = 1u;
+  const uint32_t pair_key = pair64 < kKeyBins ? static_cast<uint32_t>(pair64) : kKeyBins;
   // queue items over the positions past the split range
   uint32_t items[kRanksPerThread], it_sum = 0;
 #pragma unroll
   for (uint32_t q = 0; q < kRanksPerThread; ++q) {
     const uint32_t key = kKeyBins - 1u - (kRanksPerThread * t + q);
     const uint32_t b = st[q] > split ? st[q] : split, e = st[q] + cnt[q];
-    const uint32_t per = item_msgs(key, steps_of(a, key));
+    const uint32_t per = item_msgs(key, steps_of(a, key), pair_bucket(a, key, pair_key));
     items[q] = e > b ? (e - b + per - 1u) / per : 0u;
     it_sum += items[q];
   }
@@ -1008,7 +1043,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t item_tiles = (it_run + kBlock - 1) / kBlock;
     ctl[CTL_NITEMS] = it_run;
     ctl[CTL_SPLIT_N] = split;
-    ctl[CTL_PRIO_KEY] = static_cast<uint32_t>(2u * avg + 2u);
+    ctl[CTL_PAIR_KEY] = pair_key;
     ctl[CTL_ITEM_TILES] = item_tiles;
     ctl[CTL_TILES] = item_tiles + (ndef_chunks + kScatterChunks - 1) / kScatterChunks;
   }
@@ -1107,7 +1142,7 @@ __global__ __launch_bounds__(kBlock, kFirstWaves<V>) void k_first(PassArgs a) {
   uint32_t* const row = lds + threadIdx.x * S::kRowDw;
   Lane A[25];
   uint32_t w[S::kMaxRateDw];
-  kb::stage_block<V>(row, bc, valid ? m.len : 0u, rate_of<V>(m.var), true, w);
+  kb::stage_block<V>(row, bc, valid ? m.len : 0u, rate_of<V>(m.var), w);
   const int RW = rate_of<V>(m.var) / 4;
 #pragma unroll
   for (int k = 0; k < 50; ++k) {
@@ -1147,13 +1182,14 @@ __device__ __forceinline__ void items_tile(const PassArgs& a, uint32_t tile) {
       lo = mid + 1;
   }
   const uint32_t key = kKeyBins - 1u - lo;
-  const uint32_t per = item_msgs(key, steps_of(a, key));
+  const bool pair = pair_bucket(a, key, ctl[CTL_PAIR_KEY]);
+  const uint32_t per = item_msgs(key, steps_of(a, key), pair);
   const uint32_t first_item = lo ? iend[lo - 1] : 0u;
   const uint32_t split = ctl[CTL_SPLIT_N];  // positions before it are split work
   const uint32_t start = meta[M_START + key];
   const uint32_t b = (start > split ? start : split) + (q - first_item) * per;
   const uint32_t bucket_end = start + meta[M_FOLD + key];
-  a.items[q] = WorkItem{b, b + per < bucket_end ? b + per : bucket_end, key, 0u};
+  a.items[q] = WorkItem{b, b + per < bucket_end ? b + per : bucket_end, key, pair ? 1u : 0u};
 }
 
 // Counting-sort scatter of kScatterChunks deferred chunks: one global
@@ -1211,11 +1247,12 @@ __device__ __forceinline__ void scatter_tile(const PassArgs& a, uint32_t tile, u
 // launch's workgroups, the others spinning on a published word and then
 // fencing: on the uneven 2^20 batch the plan and tiles took 84 us of it,
 // the acquire fences of hundreds of workgroups each invalidating an L2.)
-// On each SIMD one wave (the first to claim the SIMD's flag) takes items
-// from the front at raised issue priority while they are long, so the long
-// absorb chains that bound the makespan run back to back at full rate; the
-// other resident waves take the shortest items from the back and fill the
-// issue slots the front wave leaves idle.  Both
+// On each SIMD one wave (the first to count itself on the SIMD's word) takes
+// items from the front, so the long absorb chains that bound the makespan run
+// from the start; the other resident waves take the shortest items from the
+// back.  (Every form raises and drops its priority by itself, so a front wave
+// has none of its own; being the oldest on its SIMD it still runs at 11.1 us
+// per block against 13.5 for the second wave.)  Both
 // ends of a sub-queue advance one packed 64-bit counter, so no item is taken
 // twice.  A wave drains the sub-queue of its own XCD first and then the
 // others in turn, so every item is taken whatever the mapping of waves to
@@ -1262,11 +1299,11 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
     uint32_t* row = lds + threadIdx.x * S::kRowDw;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t n_items = ctl[CTL_NITEMS];
-    const uint32_t prio_key = ctl[CTL_PRIO_KEY];
     unsigned long long* const queues = reinterpret_cast<unsigned long long*>(a.meta + M_QUEUES);
-    uint32_t claim = 0;
-    if (lane == 0) claim = atomicCAS(&a.meta[M_SIMD + simd_slot()], 0u, 1u) == 0u ? 1u : 0u;
-    const bool front = __builtin_amdgcn_readfirstlane(__shfl(claim, 0)) != 0u;
+    uint32_t rank = 0;  // of this wave among those that arrived on its SIMD
+    if (lane == 0) rank = atomicAdd(&a.meta[M_SIMD + simd_slot()], 1u);
+    rank = __builtin_amdgcn_readfirstlane(rank);
+    const bool front = rank == 0u;
     const unsigned long long step = 1ull << (front ? 0 : 32);
     const uint32_t home = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kQueues - 1u);
     // Split items first: the front waves hash the longest messages (bucketed
@@ -1277,11 +1314,9 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
     const uint32_t split_n = ctl[CTL_SPLIT_N];
     // With no split tail and no more queue items than SIMDs, the front waves
     // (one per SIMD) take every item: a second wave on a SIMD would share its
-    // issue slots and stretch both items' chains while other SIMDs idle.  The
-    // mixed-variant kernel keeps every wave claiming: in it this test alone
-    // moved the hashing code and cost the uneven batch a tenth.
-    if constexpr (V != kMixed)
-      if (!front && split_n == 0u && n_items <= a.split_cap / (kSplitItemsPerSimd * kWideStates)) return;
+    // issue slots and stretch both items' chains while other SIMDs idle.
+    if (!front && split_n == 0u && n_items <= a.split_cap / (kSplitItemsPerSimd * kWideStates))
+      return;
     {
       if (front && split_n) {
         namespace wd = kb::wide;
@@ -1320,6 +1355,12 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
         __builtin_amdgcn_s_setprio(0);
       }
     }
+    // Fewer items than waves: the second and third wave of a SIMD let the
+    // first ones of all SIMDs take an item each before they take theirs.
+    // (100003 x 1001 B SHA3-384, 1563 items: without it the early workgroups
+    // took them all, 134 SIMDs stayed idle and the launch ran 180 us, now 134.)
+    if (!front && n_items <= a.lanes / 64u)
+      for (uint32_t k = 0; k < rank; ++k) __builtin_amdgcn_s_sleep(127);
     uint32_t qi = 0;  // sub-queues tried so far
     for (;;) {
       // choose the next item; the hashing below appears once in the kernel
@@ -1342,10 +1383,13 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
       }
       if (t == 0xFFFFFFFFu) break;
       const WorkItem it = a.items[t];
-      if (front && it.key >= prio_key)
-        __builtin_amdgcn_s_setprio(3);
-      else
-        __builtin_amdgcn_s_setprio(0);
+      if (it.pair) {
+        const uint32_t h = lane % kb::pair::kPairLanes;
+        const uint32_t hi = h ? ~0u : 0u;
+        for (uint32_t pos = it.begin + lane / kb::pair::kPairLanes; pos < it.end; pos += kPairStates)
+          pair_hash_one<V>(a.data, a.offs, a.lens, a.vars, a.order[pos], a.out, a.stride, h, hi);
+        continue;
+      }
       // the next message's index and metadata are loaded while this one hashes
       uint32_t pos = it.begin + lane;
       uint64_t i = 0, off = 0, len = 0;
@@ -1374,7 +1418,6 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
         var = varn;
       }
     }
-    __builtin_amdgcn_s_setprio(0);
   }
 }
 
@@ -1514,9 +1557,9 @@ constexpr uint64_t defer_seg_of(uint64_t n) {
   return 4u * kListRun * ((runs + kCopies - 1) / kCopies);
 }
 
-// Queue items of a batch of n messages: at most ceil(n / 64) whole ones and
+// Queue items of a batch of n messages: at most ceil(n / 32) whole ones and
 // one partial item per bucket.
-uint64_t max_items(uint64_t n) { return n / 64 + kKeyBins + 1; }
+constexpr uint64_t max_items(uint64_t n) { return n / 32 + kKeyBins + 1; }
 
 // Clear a freshly allocated metadata area with a kernel on the stream (not
 // a memset: the call may be recorded into a graph).
@@ -1722,6 +1765,7 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   // at most kSplitItemsPerSimd wide split items (a state per half-wave) for
   // each SIMD's front wave (the per-bucket form takes none)
   a.split_cap = !per_bucket ? kSplitItemsPerSimd * kWideStates * 4u * static_cast<uint32_t>(cus) : 0u;
+  a.pair_cap = !per_bucket ? 2u * kPairStates * 4u * static_cast<uint32_t>(cus) : 0u;
   a.class_steps = 0;
   a.class_threads = 0;
   for (int c = 0; tile && c < KB_NB_CLASSES; ++c) {  // ranges checked by check_tile
@@ -2036,7 +2080,7 @@ constexpr uint64_t kNoAllocMax = KB_NOALLOC_MAX_MSGS;
 constexpr uint64_t kScratchOrderOff = align256(uint64_t{kMetaWords} * 4u);
 constexpr uint64_t kScratchItemsOff = kScratchOrderOff + align256(kNoAllocMax * 4u);
 constexpr uint64_t kScratchDeferredOff =
-    kScratchItemsOff + align256((kNoAllocMax / 64 + kKeyBins + 1) * sizeof(WorkItem));
+    kScratchItemsOff + align256(max_items(kNoAllocMax) * sizeof(WorkItem));
 constexpr uint64_t kScratchBytes = kScratchDeferredOff + align256(kCopies * defer_seg_of(kNoAllocMax) * 4u);
 }  // namespace
 
@@ -2069,7 +2113,7 @@ int scratch_ws(hipStream_t stream, Workspace* w) {
   w->order = reinterpret_cast<uint32_t*>(base + kScratchOrderOff);
   w->order_cap = kNoAllocMax * 4u;
   w->items = reinterpret_cast<WorkItem*>(base + kScratchItemsOff);
-  w->items_cap = (kNoAllocMax / 64 + kKeyBins + 1) * sizeof(WorkItem);
+  w->items_cap = max_items(kNoAllocMax) * sizeof(WorkItem);
   w->deferred = reinterpret_cast<uint32_t*>(base + kScratchDeferredOff);
   w->deferred_cap = kCopies * defer_seg_of(kNoAllocMax) * 4u;
   return KB_OK;

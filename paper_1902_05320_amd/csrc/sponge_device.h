@@ -1,13 +1,18 @@
 // The SHA-3 sponge (Section 3.2, eqs. 11-16) for one message per thread.
 //
-// Each block of the padded message P = M || 01 || pad10*1 is staged through a
-// per-thread row of LDS before it is xored into the state:
+// A whole block is read with unaligned 16- and 8-byte loads straight into its
+// words (the next one while the current one is permuted) and xored into the
+// state; nothing outside the message is touched.  Staging these blocks through
+// LDS like the final one cost 37 realignments, 10 LDS writes and 19 reads with
+// eight-way bank conflicts a block: 32768 x 4 KiB 346 us against 313, and the
+// mixed kernel held 207 registers instead of 175.
+//
+// The final block of the padded message P = M || 01 || pad10*1 is staged
+// through a per-thread row of LDS:
 //   1. the 16-byte-aligned chunks that hold the block's bytes are read with
-//      global_load_dwordx4 (for the next block while the current one is
-//      permuted) and stored to the row unchanged, so a block at any byte
-//      offset costs at most ceil((R + 15) / 16) vector loads;
-//   2. on the final block the bytes past the message end are cleared and the
-//      suffix/padding bytes are written with byte-granular LDS stores: 0x06
+//      global_load_dwordx4 and stored to the row unchanged, so a block at any
+//      byte offset costs at most ceil((R + 15) / 16) vector loads;
+//   2. the bytes past the message end are cleared and the suffix/padding bytes are written with byte-granular LDS stores: 0x06
 //      (bits 0,1 of the suffix "01" then the first pad bit; 0x1F for the
 //      SHAKE suffix "1111") at the message end, 0x80 (the last pad bit) on
 //      byte R-1, or the two OR-ed when both fall on byte R-1 -- the byte form
@@ -50,15 +55,18 @@ struct SpongeShape {
 __device__ __forceinline__ int rate_bytes_rt(int v) { return 200 - 2 * (v == 0 ? 28 : v == 1 ? 32 : v == 2 ? 48 : 64); }
 __device__ __forceinline__ int digest_bytes_rt(int v) { return v == 0 ? 28 : v == 1 ? 32 : v == 2 ? 48 : 64; }
 
-// The 16-byte-aligned chunks holding one block's bytes: `p` points at the
-// block's first message byte, `rem` = min(bytes left, R).  Only chunks
-// holding at least one message byte are read; the rest are zero.
+// The bytes of one block on their way into the state: for the final block the
+// 16-byte-aligned chunks that hold them (s16 = message address mod 16), for a
+// whole block its words in order.
 template <int V>
 struct BlockChunks {
   uint4 c[SpongeShape<V>::kChunks];
-  uint32_t s16;  // p mod 16
+  uint32_t s16;
 };
 
+// The final block's chunks: `p` points at its first message byte, `rem` =
+// bytes left (< R).  Only chunks holding at least one message byte are read;
+// the rest are zero.
 template <int V>
 __device__ __forceinline__ void load_block(BlockChunks<V>& bc, const uint8_t* p, uint32_t rem) {
   using S = SpongeShape<V>;
@@ -74,12 +82,65 @@ __device__ __forceinline__ void load_block(BlockChunks<V>& bc, const uint8_t* p,
   }
 }
 
-// Stage loaded chunks through `row`, apply the padding on the final block
-// (`fin`, rem < R then) and return the block as little-endian dwords
-// w[0 .. kMaxRateDw).
+// 16 and 8 bytes at any byte address (gfx950 loads them unaligned).
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t Words2 __attribute__((ext_vector_type(2), aligned(1)));
+
+template <int V>
+__device__ __forceinline__ uint32_t& chunk_dword(BlockChunks<V>& bc, int k) {
+  uint4& c = bc.c[k / 4];
+  return k % 4 == 0 ? c.x : k % 4 == 1 ? c.y : k % 4 == 2 ? c.z : c.w;
+}
+
+// The 8-byte words FROM .. TO - 1 of the block at p.
+template <int V, int FROM, int TO>
+__device__ __forceinline__ void load_words(BlockChunks<V>& bc, const uint8_t* p) {
+#pragma unroll
+  for (int i = FROM; i < TO; i += 2) {
+    if (i + 1 < TO) {
+      const Words4 v = *reinterpret_cast<const Words4*>(p + 8 * i);
+      chunk_dword<V>(bc, 2 * i) = v.x;
+      chunk_dword<V>(bc, 2 * i + 1) = v.y;
+      chunk_dword<V>(bc, 2 * i + 2) = v.z;
+      chunk_dword<V>(bc, 2 * i + 3) = v.w;
+    } else {
+      const Words2 v = *reinterpret_cast<const Words2*>(p + 8 * i);
+      chunk_dword<V>(bc, 2 * i) = v.x;
+      chunk_dword<V>(bc, 2 * i + 1) = v.y;
+    }
+  }
+}
+
+// A whole block (R bytes at p, any alignment) straight into its words, zero
+// past R: nothing is read outside the block, and its words can be xored into
+// the state as they are.  In the mixed form the lanes of a wave differ in R:
+// the words go in the four groups that the rates end at (72, 104, 136 and 144
+// bytes), three of them under a condition, rather than a condition for each
+// 16-byte chunk.
+template <int V>
+__device__ __forceinline__ void load_whole_block(BlockChunks<V>& bc, const uint8_t* p, int R) {
+  if constexpr (V == kMixed) {
+#pragma unroll
+    for (int k = 18; k < 36; ++k) chunk_dword<V>(bc, k) = 0u;
+    load_words<V, 0, 9>(bc, p);
+    if (R >= 104) {
+      load_words<V, 9, 13>(bc, p);
+      if (R >= 136) {
+        load_words<V, 13, 17>(bc, p);
+        if (R >= 144) load_words<V, 17, 18>(bc, p);
+      }
+    }
+  } else {
+    load_words<V, 0, SpongeShape<V>::kMaxRate / 8>(bc, p);
+  }
+}
+
+// Stage the final block's chunks through `row`, apply the padding (rem < R)
+// and return the block as little-endian dwords w[0 .. kMaxRateDw), garbage
+// past R.
 template <int V>
 __device__ __forceinline__ void stage_block(uint32_t* __restrict__ row, const BlockChunks<V>& bc,
-                                            uint32_t rem, int R, bool fin,
+                                            uint32_t rem, int R,
                                             uint32_t (&w)[SpongeShape<V>::kMaxRateDw]) {
   using S = SpongeShape<V>;
   const uint32_t s16 = bc.s16;
@@ -87,20 +148,18 @@ __device__ __forceinline__ void stage_block(uint32_t* __restrict__ row, const Bl
   uint4* row4 = reinterpret_cast<uint4*>(row);
 #pragma unroll
   for (int j = 0; j < S::kChunks; ++j) row4[j] = bc.c[j];
-  if (fin) {
-    // clear the tail of the last chunk: up to three whole dwords past the
-    // dword holding byte nv, then bytes nv..nv+2 (suffix byte first)
-    // (nv < s16 + R <= 4 kRowDw, so the suffix byte is always inside the row)
-    const uint32_t d0 = (nv + 3u) >> 2;
+  // clear the tail of the last chunk: up to three whole dwords past the
+  // dword holding byte nv, then bytes nv..nv+2 (suffix byte first)
+  // (nv < s16 + R <= 4 kRowDw, so the suffix byte is always inside the row)
+  const uint32_t d0 = (nv + 3u) >> 2;
 #pragma unroll
-    for (uint32_t k = 0; k < 3; ++k)
-      if (d0 + k < static_cast<uint32_t>(S::kRowDw)) row[d0 + k] = 0u;
-    uint8_t* rb = reinterpret_cast<uint8_t*>(row);
-    rb[nv] = S::kPadByte;
-    if (nv + 1u < 4u * S::kRowDw) rb[nv + 1] = 0u;
-    if (nv + 2u < 4u * S::kRowDw) rb[nv + 2] = 0u;
-    rb[s16 + R - 1] = rem + 1u == static_cast<uint32_t>(R) ? (S::kPadByte | 0x80u) : 0x80u;
-  }
+  for (uint32_t k = 0; k < 3; ++k)
+    if (d0 + k < static_cast<uint32_t>(S::kRowDw)) row[d0 + k] = 0u;
+  uint8_t* rb = reinterpret_cast<uint8_t*>(row);
+  rb[nv] = S::kPadByte;
+  if (nv + 1u < 4u * S::kRowDw) rb[nv + 1] = 0u;
+  if (nv + 2u < 4u * S::kRowDw) rb[nv + 2] = 0u;
+  rb[s16 + R - 1] = rem + 1u == static_cast<uint32_t>(R) ? (S::kPadByte | 0x80u) : 0x80u;
   const uint32_t* src = row + (s16 >> 2);
   const uint32_t sh = s16 & 3u;
 #pragma unroll
@@ -133,41 +192,41 @@ __device__ __forceinline__ void sponge_hash(Lane (&A)[25], const uint8_t* msg, u
   // blocks of the padded message: the 2 suffix bits and the pad fit after
   // any byte-aligned message, so nb = floor(L / R) + 1
   const uint64_t nb = len / static_cast<uint64_t>(R) + 1u;
+  // block b's bytes into bc
+  auto load = [&](BlockChunks<V>& bc, uint64_t b) {
+    const uint64_t off = b * static_cast<uint64_t>(R);
+    if (b + 1u == nb)
+      load_block<V>(bc, msg + off, static_cast<uint32_t>(len - off));
+    else
+      load_whole_block<V>(bc, msg + off, R);
+  };
+#pragma unroll
+  for (int k = 0; k < 25; ++k) A[k] = Lane{0u, 0u};
   BlockChunks<V> bc;
-  if (PF) load_block<V>(bc, msg, nb == 1 ? static_cast<uint32_t>(len) : static_cast<uint32_t>(R));
+  if (PF) load(bc, 0u);
   for (uint64_t b = 0; b < nb; ++b) {
     const bool fin = b + 1u == nb;
-    const uint64_t off = b * static_cast<uint64_t>(R);
-    const uint32_t rem = fin ? static_cast<uint32_t>(len - off) : static_cast<uint32_t>(R);
     absorb_phase_begin();
-    if (!PF) load_block<V>(bc, msg + off, rem);
+    if (!PF) load(bc, b);
     uint32_t w[S::kMaxRateDw];
-    stage_block<V>(row, bc, rem, R, fin, w);
-    if (PF && !fin) {
-      const uint64_t off1 = off + static_cast<uint64_t>(R);
-      load_block<V>(bc, msg + off1,
-                    b + 2u == nb ? static_cast<uint32_t>(len - off1) : static_cast<uint32_t>(R));
-    }
-    if (b == 0) {
 #pragma unroll
-      for (int k = 0; k < 50; ++k) {
-        const uint32_t v = (k < S::kMaxRateDw && k < RW) ? w[k < S::kMaxRateDw ? k : 0] : 0u;
-        if (k & 1)
-          A[k >> 1].hi = v;
-        else
-          A[k >> 1].lo = v;
-      }
-    } else {
+    for (int k = 0; k < S::kMaxRateDw; ++k) w[k] = chunk_dword<V>(bc, k);
+    if (fin) {
+      stage_block<V>(row, bc, static_cast<uint32_t>(len - b * static_cast<uint64_t>(R)), R, w);
+      if (V == kMixed) {
 #pragma unroll
-      for (int k = 0; k < S::kMaxRateDw; ++k) {
-        const uint32_t v = k < RW ? w[k] : 0u;
-        if (k & 1)
-          A[k >> 1].hi ^= v;
-        else
-          A[k >> 1].lo ^= v;
+        for (int k = 0; k < S::kMaxRateDw; ++k) w[k] = k < RW ? w[k] : 0u;
       }
     }
-    keccak_rounds_0_22(A);
+#pragma unroll
+    for (int k = 0; k < S::kMaxRateDw; ++k) {
+      if (k & 1)
+        A[k >> 1].hi ^= w[k];
+      else
+        A[k >> 1].lo ^= w[k];
+    }
+    if (PF && !fin) load(bc, b + 1u);
+    keccak_rounds_0_22_rolled(A);
     if (!fin || V >= kShake128) keccak_round(A, 23);
   }
   if (V < kShake128) keccak_round(A, 23);
@@ -287,7 +346,7 @@ __device__ __forceinline__ void sponge_hash_words(Lane (&A)[25], const uint8_t* 
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);  // this block's reads done before the area is reused
       words_to_lds<V>(msg + (b + 1u) * static_cast<uint64_t>(R), rem_of(b + 1u), area);
     }
-    keccak_rounds_0_22(A);
+    keccak_rounds_0_22_rolled(A);
     if (!fin) keccak_round(A, 23);
   }
   keccak_round(A, 23);

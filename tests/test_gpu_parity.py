@@ -149,6 +149,26 @@ def test_persistent_split_tail(kb, o2, case):
     assert (got1 == o2.sha3_batch(256, v1.data, v1.offsets, v1.lengths)).all()
 
 
+@pytest.mark.parametrize("n", [2049, 65536, 65537])
+def test_pair_items_at_their_bounds(kb, o2, n):
+    # lengths around one and several whole blocks at every offset mod 16 (whole
+    # blocks load unaligned, 32 messages to a pair wave), and the largest batch
+    # that goes to pairs whole against the smallest that does not
+    rng = np.random.Generator(np.random.PCG64(90))
+    edges = np.concatenate([[0, 1, 3, 5]] + [m * R + np.arange(-5, 6) for R in RATES for m in (1, 2, 5)])
+    lens = rng.choice(edges, n)
+    lens[:64] = 777  # no wave of one-block messages at the start
+    var = rng.integers(0, 4, n).astype(np.uint8)
+    b = wl.explicit(lens, seed=91, variant=var, gap=1, lead=3)
+    _say("pair items", n)
+    got = _gpu_mixed(kb, b)
+    want = o2.sha3_batch_mixed(b.variants, b.data, b.offsets, b.lengths)
+    assert _mismatches(got, want)[1] == 0, _mismatches(got, want)
+    for v in range(4):
+        got1 = _gpu_batch(kb, v, b)
+        assert (got1 == o2.sha3_batch(8 * DIGEST[v], b.data, b.offsets, b.lengths)).all(), v
+
+
 @pytest.mark.parametrize("mode", ["persistent", "split", "wide", "pair"])
 def test_mixed_invalid_variant_slot_is_zero(kb, o2, mode):
     b = wl.explicit([10, 200, 0, 77], seed=5, variant=np.array([1, 9, 3, 255], dtype=np.uint8))
