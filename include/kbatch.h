@@ -67,10 +67,10 @@ enum kb_mode {
                              messages per wave in arrival order (the serial absorb chain
                              of Section 3.2 runs about twice as fast per message, at a
                              fraction of the batch throughput) */
-  KB_MODE_WIDE = 4,       /* wide latency form: one 64-bit state word per lane, 32 lanes
-                             per state, two messages per wave in arrival order (each
-                             lane issues about twenty VALU instructions per round, with
-                             two exchanges through LDS; for the fewest, longest chains) */
+  KB_MODE_WIDE = 4,       /* wide latency form: half a 64-bit state word per lane, one wave
+                             per state, one message per wave in arrival order (each lane
+                             issues about a dozen VALU instructions and five lane reads
+                             per round; for the fewest, longest chains) */
   KB_MODE_PAIR = 5        /* pair form: two lanes per state, each holding one 32-bit half
                              of every state word, 32 messages per wave in arrival order
                              (about 1.5 times one thread's chain speed at a third more
@@ -99,9 +99,9 @@ typedef struct kb_tile {
   int32_t staging;          /* kb_staging: how a message's next block reaches the sponge */
   int32_t class_steps[KB_NB_CLASSES];    /* per class: steps per queue item (0 = steps_per_item) */
   int32_t class_threads[KB_NB_CLASSES];  /* per class: threads per state, 1 (one lane hashes a
-                                            message) or KB_THREADS_WIDE (the split tail: 32
-                                            lanes per state in the wide form, Section 3.2's
-                                            absorb chain about three times as fast); 0 = the
+                                            message) or KB_THREADS_WIDE (the split tail: a
+                                            wave per state in the wide form, Section 3.2's
+                                            absorb chain about four times as fast); 0 = the
                                             library's rule.  SHA-3 variants only; the split
                                             classes must be the longest ones (a class is split
                                             only if every longer class present is) */
@@ -167,7 +167,7 @@ int keccak_batch_xof(int security, const uint8_t* d_data, const uint64_t* d_offs
 /*
  * keccak_batch_xof_ex -- keccak_batch_xof with an explicit scheduling mode
  * (KB_MODE_PERSISTENT, _PLAIN, _PER_BUCKET, _SPLIT or _WIDE; in the split
- * forms five or 32 lanes share each state and squeeze it, which shortens each
+ * forms five or 50 lanes share each state and squeeze it, which shortens each
  * message's chain of permutations for a few long messages).  Same output;
  * KB_EINVAL for an unknown mode.
  */

@@ -69,6 +69,7 @@ enum : int {
   CTL_ITEM_TILES = 2,
   CTL_NDEF_CHUNKS = 3,  // chunks the first pass deferred
   CTL_MAXKEY = 4,       // largest block-count key deferred
+  CTL_SPLIT_WAVES = 5,  // waves per SIMD that take them
   CTL_SPLIT_N = 6,      // bucketed order positions [0, CTL_SPLIT_N) are hashed in the wide split form
   CTL_PAIR_KEY = 7,     // items of at least this many blocks are hashed in the pair form
   CTL_USEFUL = 8,       // uint64 (words 8, 9): block counts of the deferred messages
@@ -370,15 +371,15 @@ __global__ __launch_bounds__(kSplitBlock) void k_split(const uint8_t* __restrict
   }
 }
 
-// The wide form (one state word per lane, 32 lanes per state): absorb one
-// message into `a` (this lane's word), the next block's word loaded before
-// the current block's permutation.
+// The wide form (a wave per state, half a word per lane): absorb one message
+// into `a` (this lane's half word), the next block's word loaded before the
+// current block's permutation.  Every lane of the wave takes part.
 template <int V>
-__device__ __forceinline__ void wide_absorb(Lane& a, const uint8_t* msg, uint64_t len, int var,
+__device__ __forceinline__ void wide_absorb(uint32_t& a, const uint8_t* msg, uint64_t len, int var,
                                             const kb::wide::WideLane& L) {
   namespace wd = kb::wide;
   using S = SpongeShape<V>;
-  a = Lane{0u, 0u};
+  a = 0u;
   const int R = rate_of<V>(var);
   const uint32_t sh = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(msg) & 3u);
   const uint64_t nb = len / static_cast<uint64_t>(R) + 1u;
@@ -393,29 +394,24 @@ __device__ __forceinline__ void wide_absorb(Lane& a, const uint8_t* msg, uint64_
   }
 }
 
-// XOF squeeze in the wide form (Section 3.2): each lane writes its word when
-// it lies in the rate, r bits of output per permutation, until out_len bytes
-// are out.  Bytes are stored one by one unless out_len is a multiple of 4
+// XOF squeeze in the wide form (Section 3.2): each lane writes a dword of its
+// word when that lies in the rate, r bits of output per permutation, until
+// out_len bytes are out.  Bytes are stored one by one unless out_len is a multiple of 4
 // and `out` is 4-byte aligned.
 template <int V>
-__device__ __forceinline__ void wide_xof(Lane& a, uint8_t* out, uint64_t out_len,
+__device__ __forceinline__ void wide_xof(uint32_t& a, uint8_t* out, uint64_t out_len,
                                          const kb::wide::WideLane& L) {
   constexpr uint32_t R = SpongeShape<V>::kMaxRate;
   const bool words = (out_len & 3u) == 0 && (reinterpret_cast<uintptr_t>(out) & 3u) == 0;
   for (uint64_t done = 0;;) {
-    if (8u * L.word < R) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t v = h ? a.hi : a.lo;
-        const uint64_t at = done + 8u * L.word + 4u * h;
-        if (at < out_len) {
-          if (words) {
-            *reinterpret_cast<uint32_t*>(out + at) = v;
-          } else {
-            for (uint32_t q = 0; q < 4u && at + q < out_len; ++q)
-              out[at + q] = static_cast<uint8_t>(v >> (8u * q));
-          }
-        }
+    const uint32_t v = kb::wide::output_dword(a, L);
+    const uint64_t at = done + 8u * L.word + 4u * L.half;
+    if (8u * L.word < R && at < out_len) {
+      if (words) {
+        *reinterpret_cast<uint32_t*>(out + at) = v;
+      } else {
+        for (uint32_t q = 0; q < 4u && at + q < out_len; ++q)
+          out[at + q] = static_cast<uint8_t>(v >> (8u * q));
       }
     }
     done += R;
@@ -424,11 +420,10 @@ __device__ __forceinline__ void wide_xof(Lane& a, uint8_t* out, uint64_t out_len
   }
 }
 
-// Wide form: each half of a wave hashes one message at a time, message
-// order[first + p] (or first + p) for p = state, state + states, ...  One
-// wave per workgroup, as in the five-lane form.
-constexpr int kWideBlock = 64;
-constexpr int kWideStates = kWideBlock / kb::wide::kHalfLanes;
+// Wide form: each wave hashes one message at a time, message order[first + p]
+// (or first + p) for p = wave, wave + waves, ...  One wave per workgroup, as
+// in the five-lane form.
+constexpr int kWideBlock = kb::wide::kStateLanes;
 
 template <int V>
 __global__ __launch_bounds__(kWideBlock) void k_wide(const uint8_t* __restrict__ data,
@@ -439,15 +434,12 @@ __global__ __launch_bounds__(kWideBlock) void k_wide(const uint8_t* __restrict__
                                                      uint64_t first, uint64_t count,
                                                      uint8_t* __restrict__ out, uint64_t stride) {
   namespace wd = kb::wide;
-  __shared__ __align__(16) uint64_t lds[kWideStates * wd::kAreaSlots];
-  const uint32_t s = threadIdx.x / wd::kHalfLanes, h = threadIdx.x % wd::kHalfLanes;
   wd::WideLane L;
-  wd::setup(L, h, lds + s * wd::kAreaSlots);
-  const uint64_t states = static_cast<uint64_t>(gridDim.x) * kWideStates;
+  wd::setup(L, threadIdx.x);
   const int slot_dw = V == kMixed ? 16 : V >= kShake128 ? 0 : kb::digest_bytes_of(V) / 4;
-  for (uint64_t p = static_cast<uint64_t>(blockIdx.x) * kWideStates + s; p < count; p += states) {
+  for (uint64_t p = blockIdx.x; p < count; p += gridDim.x) {
     const uint64_t i = order ? order[first + p] : first + p;
-    Lane a;
+    uint32_t a;
     if constexpr (V >= kShake128) {
       wide_absorb<V>(a, data + offs[i], lens[i], V, L);
       wide_xof<V>(a, out + i * stride, stride, L);
@@ -456,7 +448,7 @@ __global__ __launch_bounds__(kWideBlock) void k_wide(const uint8_t* __restrict__
     const int var = V == kMixed ? vars[i] : V;
     uint32_t* o = reinterpret_cast<uint32_t*>(out + i * stride);
     if (V == kMixed && var > 3) {  // no such variant: the slot is zeroed
-      wd::store_word(o, Lane{0u, 0u}, 0, slot_dw, L);
+      wd::store_word(o, 0u, 0, slot_dw, L);
       continue;
     }
     wide_absorb<V>(a, data + offs[i], lens[i], var, L);
@@ -594,8 +586,8 @@ struct TreeLevels {
 // workgroup's subtree, where one thread per pair would leave a wave's worth
 // of permutation latency for a handful of lanes, hash one pair per group in
 // the lane-split form (five lanes per state, about twice as fast per
-// permutation), and the levels of at most one pair per half-wave in the wide
-// form (one state word per lane, about three times as fast).  The exchange
+// permutation), and the levels of at most one pair per wave in the wide form
+// (half a state word per lane, about four times as fast).  The exchange
 // areas reuse the staging rows, which no level uses after the first split
 // one.
 //
@@ -627,9 +619,7 @@ __global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, ui
   constexpr int kStageDw = W8 ? kWordsDw : T * S::kRowDw;
   __shared__ __align__(16) uint32_t lds[kStageDw > kSplitDw ? kStageDw : kSplitDw];
   static_assert(kSplitDw <= T * S::kRowDw, "the split exchange area fits in the staging rows");
-  constexpr int kWideStatesT = T / kb::wide::kHalfLanes;
-  static_assert(2 * kWideStatesT * kb::wide::kAreaSlots <= (kStageDw > kSplitDw ? kStageDw : kSplitDw),
-                "the wide exchange areas fit in the kernel's LDS");
+  constexpr uint32_t kWaves = T / kb::wide::kStateLanes;
   uint32_t* row = lds + (W8 ? 0u : threadIdx.x * S::kRowDw);
   // one message of whole words (W8: through this wave's LDS area) or of any
   // bytes (staged through this thread's row)
@@ -648,6 +638,8 @@ __global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, ui
     return level == top ? root : nodes + lv.off[level] + j * D;
   };
   static_assert(NODES == T || NODES == 2 * T, "one or two nodes per thread");
+  kb::wide::WideLane wide_lane;
+  if constexpr (WL) kb::wide::setup(wide_lane, threadIdx.x & 63u);
   if (NODES == T && first == 0) {  // leaves: only launches with one node per thread take level 0
     const uint64_t i = w * T + threadIdx.x;
     if (i < lv.m[0]) {
@@ -662,23 +654,22 @@ __global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, ui
     const int l = first + k;  // reading level l, writing level l + 1
     __syncthreads();
     const uint64_t span = static_cast<uint64_t>(NODES) >> (k + 1);  // pairs of this workgroup
-    if (WL && span <= static_cast<uint64_t>(kWideStatesT)) {
-      // one pair per half-wave in the wide form (one state word per lane)
+    if (WL && span <= kWaves) {
+      // one pair per wave in the wide form
       namespace wd = kb::wide;
-      const uint32_t st = threadIdx.x / wd::kHalfLanes, h = threadIdx.x % wd::kHalfLanes;
-      const uint64_t j = w * span + st;
-      if (st < span && j < lv.m[l + 1]) {
+      const uint32_t lane = threadIdx.x & 63u;
+      const uint32_t p = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
+      const uint64_t j = w * span + p;
+      if (p < span && j < lv.m[l + 1]) {
         const uint8_t* src = nodes + lv.off[l] + 2 * j * D;
         uint32_t* d32 = reinterpret_cast<uint32_t*>(dst_of(l + 1, j));
         if (2 * j + 1 < lv.m[l]) {
-          wd::WideLane L;
-          wd::setup(L, h, reinterpret_cast<uint64_t*>(lds) + st * wd::kAreaSlots);
-          Lane a;
-          wide_absorb<V>(a, src, 2 * D, V, L);
-          wd::store_word(d32, a, static_cast<int>(D / 4), static_cast<int>(D / 4), L);
+          uint32_t a;
+          wide_absorb<V>(a, src, 2 * D, V, wide_lane);
+          wd::store_word(d32, a, static_cast<int>(D / 4), static_cast<int>(D / 4), wide_lane);
         } else {
           const uint32_t* s32 = reinterpret_cast<const uint32_t*>(src);
-          for (uint32_t q = h; q < D / 4; q += wd::kHalfLanes) d32[q] = s32[q];
+          if (lane < D / 4) d32[lane] = s32[lane];
         }
       }
     } else if (!kSplitLevels || span > static_cast<uint64_t>(kGroups)) {
@@ -858,7 +849,7 @@ constexpr uint32_t kRanksPerThread = kKeyBins / kBlock;
 // max(kSplitMinKey, 2 x the blocks per resident lane) blocks, at most
 // `split_cap` of them (twice that when every deferred message qualifies).
 // Below the second bound the batch's throughput, not
-// its longest chain, sets the time, and a split item (two messages per wave)
+// its longest chain, sets the time, and a split item (one message per wave)
 // costs throughput.  (An earlier bound of 4 x the mean block count kept a
 // batch of a few equal long messages out of the split form: 8 x 64 KiB ran
 // at 11.0 us per block of the chain, now 3.8.)
@@ -880,11 +871,14 @@ constexpr uint32_t kSplitMinKey = 32;
 // Between the two (one item or so per wave) one thread per message keeps the
 // waves of a SIMD at two: 100003 x 1001 B SHA3-384 291 us, 320 with pairs.
 constexpr uint64_t kPairDeepEighths = 12;
-// Wide split items per SIMD's front wave.  Two measured against one
-// (interleaved A/B): serving stream p50 5.23-5.25 against 5.17 ms, p99
-// 7.87-7.95 against 7.70-7.78 ms; 4096 x 16 KiB 8.6 against 14.2 us per
-// block of the chain; the uneven batch level.  One keeps the serving tail.
-constexpr uint32_t kSplitItemsPerSimd = 1;
+// Wide split items (messages) per SIMD.  A SIMD's front wave takes them one
+// after the other, unless the middle one is longer than 3/5 of the longest:
+// then a second wave takes its share at the same time.  Alone on its SIMD a
+// chain runs at 2.4 us per block, two share it at 2.9-3.4, so the second wave
+// pays where two of the items in turn would outlast the longest one.  2048 x
+// 16 KiB 3.4 us per block of the chain with two waves, 5.3 with one; the
+// serving burst, whose lengths spread over decades, 2.55 ms against 2.17-2.50.
+constexpr uint32_t kSplitItemsPerSimd = 2;
 
 // The plan, made by one workgroup of the second pass once the first pass
 // has finished.  Folds the partial histograms, writes the bucket
@@ -895,7 +889,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   uint32_t* const meta = a.meta;
   uint32_t* const ctl = meta + M_CTL;
   uint32_t* const sync = meta + M_SYNC;
-  __shared__ uint32_t s_split, s_ndef, s_maxkey;
+  __shared__ uint32_t s_split, s_ndef, s_maxkey, s_midkey;
   __shared__ unsigned long long s_useful;
   const uint32_t t = threadIdx.x;
   // The deferred sub-lists' lengths (read into a scalar register: the branch
@@ -912,7 +906,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   dirty = __builtin_amdgcn_readfirstlane(dirty);
   if (t == 0) {
     s_useful = 0ull;
-    s_maxkey = 0u;
+    s_maxkey = s_midkey = 0u;
   }
   __syncthreads();  // every thread has read the counters
   if (t < kCopies) meta[M_DEFCNT + t * kLine] = 0u;
@@ -1001,6 +995,8 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t ct = (a.class_threads >> (4u * class_of_key(key))) & 0xFu;
     const bool split_here = ct == 2u || (ct == 0u && key >= kmin);
     if (cnt[q] && !split_here) atomicMin(&s_split, st[q]);
+    const uint32_t mid = a.split_cap / kSplitItemsPerSimd;  // the first item past one per SIMD
+    if (st[q] <= mid && mid < st[q] + cnt[q]) s_midkey = key;
   }
   __syncthreads();
   const uint32_t split_all = __builtin_amdgcn_readfirstlane(s_split);
@@ -1043,6 +1039,8 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t item_tiles = (it_run + kBlock - 1) / kBlock;
     ctl[CTL_NITEMS] = it_run;
     ctl[CTL_SPLIT_N] = split;
+    ctl[CTL_SPLIT_WAVES] =
+        split > a.split_cap / kSplitItemsPerSimd && 5u * s_midkey > 3u * s_maxkey ? 2u : 1u;
     ctl[CTL_PAIR_KEY] = pair_key;
     ctl[CTL_ITEM_TILES] = item_tiles;
     ctl[CTL_TILES] = item_tiles + (ndef_chunks + kScatterChunks - 1) / kScatterChunks;
@@ -1265,8 +1263,6 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
   constexpr uint32_t kLdsDw = kStageDw > 2 * kKeyBins ? kStageDw : 2 * kKeyBins;
   __shared__ __align__(16) uint32_t lds[kLdsDw];
   __shared__ uint32_t s_tile;
-  static_assert(2 * kWideStates * kb::wide::kAreaSlots <= 64 * S::kRowDw,
-                "a wave's staging rows hold its wide exchange areas");
   const uint32_t* ctl = a.meta + M_CTL;
   uint32_t* const sync = a.meta + M_SYNC;
   if constexpr (PH == 0) {
@@ -1307,49 +1303,42 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
     const unsigned long long step = 1ull << (front ? 0 : 32);
     const uint32_t home = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kQueues - 1u);
     // Split items first: the front waves hash the longest messages (bucketed
-    // positions [0, split_n)) two at a time, one per half-wave, in the wide
-    // lane-split form (one state word per lane), whose chain of permutations
-    // runs about three times as fast as one thread's.  The exchange areas are
-    // this wave's own staging rows.  The XOFs squeeze in the same form.
+    // positions [0, split_n)) one at a time in the wide lane-split form (half a
+    // state word per lane), whose chain of permutations runs about four times
+    // as fast as one thread's.  The XOFs squeeze in the same form.
     const uint32_t split_n = ctl[CTL_SPLIT_N];
     // With no split tail and no more queue items than SIMDs, the front waves
     // (one per SIMD) take every item: a second wave on a SIMD would share its
     // issue slots and stretch both items' chains while other SIMDs idle.
-    if (!front && split_n == 0u && n_items <= a.split_cap / (kSplitItemsPerSimd * kWideStates))
-      return;
+    if (!front && split_n == 0u && n_items <= a.split_cap / kSplitItemsPerSimd) return;
     {
-      if (front && split_n) {
+      if (split_n && rank < ctl[CTL_SPLIT_WAVES]) {
+        if (rank) __builtin_amdgcn_s_sleep(127);  // the front waves of all SIMDs first
         namespace wd = kb::wide;
-        uint64_t* area = reinterpret_cast<uint64_t*>(lds + (threadIdx.x & ~63u) * S::kRowDw);
-        const uint32_t half = lane / wd::kHalfLanes;
         wd::WideLane L;
-        wd::setup(L, lane % wd::kHalfLanes, area + half * wd::kAreaSlots);
+        wd::setup(L, lane);
         const int slot_dw = V >= kShake128 ? 0 : static_cast<int>(out_stride_of<V <= kMixed ? V : 1>() / 4u);
         uint32_t* split_ctr = reinterpret_cast<uint32_t*>(queues + kQueues * (kLine / 2));
         __builtin_amdgcn_s_setprio(3);
         for (;;) {
-          uint32_t d = 0;
+          uint32_t pos = 0;
           if (lane == 0)
-            d = __hip_atomic_fetch_add(split_ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          d = __builtin_amdgcn_readfirstlane(__shfl(d, 0));
-          if (d >= (split_n + kWideStates - 1u) / kWideStates) break;
-          const uint32_t pos = d * kWideStates + half;
-          if (pos < split_n) {
-            const uint32_t i = a.order[pos];
-            const int var = V == kMixed ? a.vars[i] : V;
-            uint32_t* o = reinterpret_cast<uint32_t*>(a.out + static_cast<uint64_t>(i) * a.stride);
-            if constexpr (V >= kShake128) {
-              Lane w;
-              wide_absorb<V>(w, a.data + a.offs[i], a.lens[i], V, L);
-              wide_xof<V>(w, a.out + static_cast<uint64_t>(i) * a.stride, a.stride, L);
-            } else if (V == kMixed && var > 3) {
-              wd::store_word(o, Lane{0u, 0u}, 0, slot_dw, L);
-            } else {
-              Lane w;
-              wide_absorb<V>(w, a.data + a.offs[i], a.lens[i], var, L);
-              const int dw = V == kMixed ? kb::digest_bytes_rt(var) / 4 : kb::digest_bytes_of(V) / 4;
-              wd::store_word(o, w, dw, slot_dw, L);
-            }
+            pos = __hip_atomic_fetch_add(split_ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          pos = __builtin_amdgcn_readfirstlane(pos);
+          if (pos >= split_n) break;
+          const uint32_t i = a.order[pos];
+          const int var = V == kMixed ? a.vars[i] : V;
+          uint32_t* o = reinterpret_cast<uint32_t*>(a.out + static_cast<uint64_t>(i) * a.stride);
+          uint32_t w;
+          if constexpr (V >= kShake128) {
+            wide_absorb<V>(w, a.data + a.offs[i], a.lens[i], V, L);
+            wide_xof<V>(w, a.out + static_cast<uint64_t>(i) * a.stride, a.stride, L);
+          } else if (V == kMixed && var > 3) {
+            wd::store_word(o, 0u, 0, slot_dw, L);
+          } else {
+            wide_absorb<V>(w, a.data + a.offs[i], a.lens[i], var, L);
+            const int dw = V == kMixed ? kb::digest_bytes_rt(var) / 4 : kb::digest_bytes_of(V) / 4;
+            wd::store_word(o, w, dw, slot_dw, L);
           }
         }
         __builtin_amdgcn_s_setprio(0);
@@ -1661,7 +1650,7 @@ int launch_wide(const Batch& b, const uint32_t* order, uint64_t first, uint64_t 
   int rc = cu_count(dev, &cus);
   if (rc) return rc;
   // one state per message up to 16 waves per CU; beyond that states loop
-  uint64_t grid = (count + kWideStates - 1) / kWideStates;
+  uint64_t grid = count;
   if (grid > static_cast<uint64_t>(16 * cus)) grid = 16 * cus;
   {
     TimedLaunch tl(s, KB_KERNEL_WIDE);
@@ -1762,9 +1751,8 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   a.order = w.order;
   a.items = w.items;
   a.steps = tile && tile->steps_per_item > 0 ? static_cast<uint32_t>(tile->steps_per_item) : 4u;
-  // at most kSplitItemsPerSimd wide split items (a state per half-wave) for
-  // each SIMD's front wave (the per-bucket form takes none)
-  a.split_cap = !per_bucket ? kSplitItemsPerSimd * kWideStates * 4u * static_cast<uint32_t>(cus) : 0u;
+  // at most kSplitItemsPerSimd wide split items (one message) for each SIMD's front wave (the per-bucket form takes none)
+  a.split_cap = !per_bucket ? kSplitItemsPerSimd * 4u * static_cast<uint32_t>(cus) : 0u;
   a.pair_cap = !per_bucket ? 2u * kPairStates * 4u * static_cast<uint32_t>(cus) : 0u;
   a.class_steps = 0;
   a.class_threads = 0;

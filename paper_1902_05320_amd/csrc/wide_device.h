@@ -1,31 +1,36 @@
-// Wide lane-split sponge: one Keccak-f[1600] state per 32 lanes of a wave,
-// one 64-bit state word per lane (lanes 25..31 of each half idle), two
-// messages per wave.  The serial absorb chain of one message (Section 3.2)
-// then costs each lane about twenty VALU instructions per round instead of
-// the ~180 of one thread per message or the ~86 of the five-lane form; the
-// price is two exchanges through LDS per round.
+// Wide lane-split sponge: one Keccak-f[1600] state per wave, one 32-bit half
+// of a state word per lane, held bit-interleaved: half 0 of a word is its even
+// bits, half 1 its odd bits.  The serial absorb chain of one message (Section
+// 3.2) then costs each lane about a dozen VALU instructions and five lane
+// reads per round.
 //
-// Lane i of a half holds word i = x + 5y (Section 3.1, eq. 1).  Each half
-// owns an LDS area of kAreaSlots 64-bit slots:
-//   theta area  slots 6x + y: column x, padded to six slots (48 bytes) so
-//               that a column is read with two 16-byte and one 8-byte load
-//   chi area    slots 30 + 10y + x and 30 + 10y + x + 5: row y written twice,
-//               so that words x, x+1, x+2 (mod 5) of a row lie at three
-//               consecutive slots
-//   spare       slot 80, written by the idle lanes
-// Per round (eq. 10):
-//   theta  every lane writes its word to the theta area and reads columns
-//          x - 1 and x + 1, so it forms C[x-1] and C[x+1] itself and applies
-//          D[x] = C[x-1] ^ rot(C[x+1], 1) to its word (eqs. 2-4);
-//   rho    rotates by the lane's own amount (eq. 5);
-//   pi     is where the word is written in the chi area: word (x, y) goes to
-//          (y, 2x + 3y) (eq. 6);
-//   chi    reads its row neighbours x + 1 and x + 2 (eq. 7);
-//   iota   lane 0 only (eqs. 8-9).
-// The exchanges rely on a wave's LDS operations executing in issue order:
-// every lane's write precedes the reads of the same round, and a slot is
-// written again only after the reads of the previous round have returned
-// (the new value depends on them).
+// Bit-interleaving (a published technique of 32-bit Keccak code: Bertoni et
+// al., "Keccak implementation overview") makes every rotation local: rotating
+// a word by 2k rotates both halves by k; rotating it by 2k + 1 swaps the
+// halves, the even ones rotated by k and the odd ones by k + 1 before.  A swap
+// is only a different source lane.  So no lane ever needs its partner half.
+//
+// Lane layout: the five words of column x, half h, sit in five neighbouring
+// lanes of one 16-lane row, group g = 2x + h in row g / 3 at lanes
+// 5 (g % 3) + y.  Per round (eq. 10):
+//   theta  column parities by three row shifts (DPP), complete in the lane of
+//          y = 4; every lane then reads C[x-1] and, of the other half,
+//          C[x+1] from those lanes (ds_bpermute) and applies
+//          D = C[x-1] ^ rot(C[x+1], 1) (eqs. 2-4);
+//   rho    one rotation by the lane's own amount (eq. 5);
+//   pi     is where chi reads from (eq. 6);
+//   chi    reads words x, x + 1, x + 2 of its row (three ds_bpermute, eq. 7);
+//   iota   is linear, so that of round r is folded into round r + 1's theta:
+//          the constant reaches word (0, 0) and, through the parity of column
+//          0, the columns 1 and 4, one xor off the critical path (eqs. 8-9).
+// What bounds it is latency: two lane-read round trips of 56 cycles and a
+// chain of about ten dependent VALU instructions (6.5 cycles each, 13 through
+// DPP).  Measured on one wave alone, per permutation: 2.15 us, against 3.03
+// for one 64-bit word per lane with both exchanges through LDS memory (two
+// states per wave); with 2048 states on the chip (two waves per SIMD against
+// one) 2.79 against 3.75, with 4096 5.6 against 5.5.  Column parities through
+// LDS memory instead of DPP: 2.07 alone, but 4.1 with two waves per SIMD (the
+// reads of ten words per lane fill the LDS).
 #pragma once
 
 #include "sponge_device.h"
@@ -33,103 +38,172 @@
 namespace kb {
 namespace wide {
 
-constexpr int kHalfLanes = 32;   // lanes per state
-constexpr int kThetaSlots = 30;
-constexpr int kChiBase = 30;
-constexpr int kSpare = 80;
-constexpr int kAreaSlots = 82;   // 656 bytes, a multiple of 16
+constexpr int kStateLanes = 64;  // lanes per state
+
+// Bits h, h + 2, h + 4, ... of a 64-bit word.
+constexpr uint32_t half_bits(uint64_t v, int h) {
+  uint32_t r = 0;
+  for (int i = 0; i < 32; ++i) r |= static_cast<uint32_t>((v >> (2 * i + h)) & 1u) << i;
+  return r;
+}
+
+struct HalfConstants {
+  uint32_t e[24], o[24];
+};
+constexpr HalfConstants make_half_constants() {
+  HalfConstants t{};
+  for (int r = 0; r < 24; ++r) {
+    const uint64_t v = (static_cast<uint64_t>(kRC.hi[r]) << 32) | kRC.lo[r];
+    t.e[r] = half_bits(v, 0);
+    t.o[r] = half_bits(v, 1);
+  }
+  return t;
+}
+constexpr HalfConstants kHalfRC = make_half_constants();
+
+// The 25 rotation amounts, ten 6-bit fields to a constant, and their parities.
+struct RotTable {
+  uint64_t six[3];
+  uint32_t odd;
+};
+constexpr RotTable make_rot_table() {
+  RotTable t{};
+  for (int i = 0; i < 25; ++i) {
+    t.six[i / 10] |= static_cast<uint64_t>(kMaps.rot[i]) << (6 * (i % 10));
+    t.odd |= static_cast<uint32_t>(kMaps.rot[i] & 1) << i;
+  }
+  return t;
+}
+constexpr RotTable kRot = make_rot_table();
 
 // Per-lane constants of the wide form.
 struct WideLane {
-  uint32_t word;       // state word of this lane (25 and up: idle)
-  uint32_t sh;         // rho: v_alignbit amount
-  bool swap;           // rho: swap the halves first
-  uint32_t iota;       // all ones on word 0
-  uint64_t* tw;        // theta write slot
-  const uint64_t* cm;  // column x - 1
-  const uint64_t* cp;  // column x + 1
-  uint64_t* pw0;       // pi destination, both copies of its row
-  uint64_t* pw1;
-  const uint64_t* cr;  // row neighbours x, x + 1, x + 2 of this lane's word after pi
+  uint32_t word;        // state word of this lane (25: idle lane)
+  uint32_t half;        // 0: its even bits, 1: its odd bits
+  uint32_t cm, cp;      // lane reads (byte addresses): C[x-1] of this half, C[x+1] of the other
+  uint32_t b0, b1, b2;  // words x, x + 1, x + 2 of this row after rho and pi
+  uint32_t partner;     // the other half of this word
+  uint32_t one;         // theta's rotation by one, as a v_alignbit amount
+  uint32_t sh;          // rho's
+  uint32_t m1, m2, m3;  // lanes whose folded iota constant is RC's even bits, odd bits, odd bits rotated
+  uint32_t origin;      // all ones on word (0, 0)
 };
 
-// `h` is the lane's index in its half, `area` the half's kAreaSlots slots
-// (16-byte aligned).
-__device__ __forceinline__ void setup(WideLane& L, uint32_t h, uint64_t* area) {
-  const bool on = h < 25u;
-  const uint32_t i = on ? h : 0u;
-  const uint32_t x = i % 5u, y = i / 5u;
-  int n = 0;
-#pragma unroll
-  for (int k = 0; k < 25; ++k)
-    if (static_cast<int>(i) == k) n = kMaps.rot[k];
-  // rotl(v, n) as in the five-lane form: for 0 < n < 32 alignbit by 32 - n;
-  // n = 32 is alignbit by 0 (a swap); n > 32 and n = 0 swap first
-  L.swap = n == 0 || n > 32;
-  L.sh = static_cast<uint32_t>((32 - (n & 31)) & 31);
-  L.word = h;
-  L.iota = h == 0u ? ~0u : 0u;
-  L.tw = on ? area + 6u * x + y : area + kSpare;
-  L.cm = area + 6u * ((x + 4u) % 5u);
-  L.cp = area + 6u * ((x + 1u) % 5u);
-  // pi: word (x, y) becomes word (y, 2x + 3y)
-  const uint32_t px = y, py = (2u * x + 3u * y) % 5u;
-  L.pw0 = on ? area + kChiBase + 10u * py + px : area + kSpare;
-  L.pw1 = on ? area + kChiBase + 10u * py + px + 5u : area + kSpare;
-  L.cr = area + kChiBase + 10u * y + x;
+// Byte address of the lane that holds half h of word i.
+__device__ __forceinline__ uint32_t lane_address(uint32_t i, uint32_t h) {
+  const uint32_t g = (i % 5u) * 2u + h;
+  return 4u * ((g / 3u) * 16u + (g % 3u) * 5u + i / 5u);
 }
 
-__device__ __forceinline__ uint64_t pack(Lane v) {
-  return static_cast<uint64_t>(v.lo) | (static_cast<uint64_t>(v.hi) << 32);
-}
-__device__ __forceinline__ Lane unpack(uint64_t v) {
-  return Lane{static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32)};
+__device__ __forceinline__ void setup(WideLane& L, uint32_t lane) {
+  const uint32_t s = lane & 15u, g0 = (lane >> 4) * 3u + s / 5u;
+  const bool on = s < 15u && g0 < 10u;
+  const uint32_t g = on ? g0 : 0u, y = on ? s % 5u : 0u;
+  const uint32_t x = g >> 1, h = g & 1u, i = x + 5u * y;
+  L.word = on ? i : 25u;
+  L.half = h;
+  const uint64_t six = i < 10u ? kRot.six[0] : i < 20u ? kRot.six[1] : kRot.six[2];
+  const uint32_t n = static_cast<uint32_t>(six >> (6u * (i % 10u))) & 63u;
+  // n = 2k: by k; n = 2k + 1: the even bits by k, the odd ones by k + 1
+  const uint32_t amount = (n + ((n & 1u) & h)) >> 1;
+  L.sh = (32u - amount) & 31u;
+  // rotl(C, 1): its even bits are C's odd ones rotated by one, its odd bits C's even ones
+  L.one = h == 0u ? 31u : 0u;
+  L.cm = lane_address((x + 4u) % 5u + 20u, h);
+  L.cp = lane_address((x + 1u) % 5u + 20u, h ^ 1u);
+  // pi sends word (y, 2x' + 3y) = (X, Y) from (x', y): x' = 3Y + X mod 5, y = X;
+  // an odd rotation moves the half across
+  auto source = [&](uint32_t X) -> uint32_t {
+    const uint32_t j = (3u * y + X) % 5u + 5u * X;
+    return lane_address(j, h ^ ((kRot.odd >> j) & 1u));
+  };
+  L.b0 = source(x);
+  L.b1 = source((x + 1u) % 5u);
+  L.b2 = source((x + 2u) % 5u);
+  L.partner = lane_address(i, h ^ 1u);
+  const bool direct = i == 0u || x == 1u, rotated = x == 4u;
+  L.m1 = on && ((direct && h == 0u) || (rotated && h == 1u)) ? ~0u : 0u;
+  L.m2 = on && direct && h == 1u ? ~0u : 0u;
+  L.m3 = on && rotated && h == 0u ? ~0u : 0u;
+  L.origin = on && i == 0u ? ~0u : 0u;
 }
 
-// Column parity of the five words at `col` (two 16-byte and one 8-byte LDS load).
-__device__ __forceinline__ Lane column_parity(const uint64_t* col) {
-  const uint4 w01 = reinterpret_cast<const uint4*>(col)[0];
-  const uint4 w23 = reinterpret_cast<const uint4*>(col)[1];
-  const uint2 w4 = reinterpret_cast<const uint2*>(col)[4];
-  return Lane{xor3(xor3(w01.x, w01.z, w23.x), w23.z, w4.x), xor3(xor3(w01.y, w01.w, w23.y), w23.w, w4.y)};
+__device__ __forceinline__ uint32_t read_lane(uint32_t address, uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(static_cast<int>(address), static_cast<int>(v)));
 }
 
-// One round (eq. 10) on the half's state, one word per lane.
-__device__ __forceinline__ void wide_round(Lane& a, const WideLane& L, int r) {
-  // theta (eqs. 2-4)
-  *L.tw = pack(a);
-  __asm__ volatile("" ::: "memory");
-  const Lane cm = column_parity(L.cm);
-  const Lane cp = column_parity(L.cp);
-  __asm__ volatile("" ::: "memory");
-  const Lane d = rotl(cp, 1);
-  a.lo = xor3(a.lo, cm.lo, d.lo);
-  a.hi = xor3(a.hi, cm.hi, d.hi);
-  // rho (eq. 5) by the lane's amount
-  {
-    const uint32_t lo = L.swap ? a.hi : a.lo, hi = L.swap ? a.lo : a.hi;
-    a = Lane{__builtin_amdgcn_alignbit(lo, hi, L.sh), __builtin_amdgcn_alignbit(hi, lo, L.sh)};
+// w ^ (v shifted up N lanes within its row of 16)
+template <int N>
+__device__ __forceinline__ uint32_t xor_row_shift(uint32_t w, uint32_t v) {
+  return w ^ static_cast<uint32_t>(
+                 __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x110 + N, 0xf, 0xf, true));
+}
+
+// One round (eq. 10), its iota left to the next one; `r` must fold to a
+// constant.  Round 0 takes a state whose last iota has been applied.
+__device__ __forceinline__ void wide_round(uint32_t& a, const WideLane& L, int r) {
+  // theta (eqs. 2-4): in the lane of y = 4, pairs (3, 4) and 0, then (1, 2)
+  const uint32_t q = xor_row_shift<1>(a, a);
+  const uint32_t p = xor_row_shift<4>(q, a);
+  const uint32_t c = xor_row_shift<2>(p, q);
+  const uint32_t cp = read_lane(L.cp, c);
+  const uint32_t cm = read_lane(L.cm, c);
+  uint32_t ak = a;
+  if (r > 0) {
+    const uint32_t e = kHalfRC.e[r - 1], o = kHalfRC.o[r - 1];
+    uint32_t m1 = L.m1, m2 = L.m2, m3 = L.m3;
+    // (through an empty asm so that the masked constants are formed round by
+    // round, not hoisted into registers)
+    __asm__ volatile("" : "+v"(m1), "+v"(m2), "+v"(m3));
+    if (e) ak ^= m1 & e;
+    if (o) ak ^= (m2 & o) | (m3 & ((o << 1) | (o >> 31)));
   }
-  // pi (eq. 6) as the write position, chi (eq. 7) along the row
-  const uint64_t v = pack(a);
-  *L.pw0 = v;
-  *L.pw1 = v;
-  __asm__ volatile("" ::: "memory");
-  const Lane b0 = unpack(L.cr[0]), b1 = unpack(L.cr[1]), b2 = unpack(L.cr[2]);
-  __asm__ volatile("" ::: "memory");
-  a.lo = b0.lo ^ (~b1.lo & b2.lo);
-  a.hi = b0.hi ^ (~b1.hi & b2.hi);
-  // iota (eqs. 8-9) on word 0 (the mask passes through an empty asm so the
-  // masked constants are formed round by round, not hoisted into registers)
-  uint32_t m = L.iota;
-  __asm__ volatile("" : "+v"(m));
-  if (kRC.lo[r]) a.lo ^= m & kRC.lo[r];
-  if (kRC.hi[r]) a.hi ^= m & kRC.hi[r];
+  const uint32_t d = __builtin_amdgcn_alignbit(cp, cp, L.one);
+  a = xor3(ak, cm, d);
+  // rho (eq. 5), pi (eq. 6) and chi (eq. 7)
+  const uint32_t v = __builtin_amdgcn_alignbit(a, a, L.sh);
+  const uint32_t b1 = read_lane(L.b1, v);
+  const uint32_t b2 = read_lane(L.b2, v);
+  const uint32_t b0 = read_lane(L.b0, v);
+  a = b0 ^ (~b1 & b2);
 }
 
-__device__ __forceinline__ void wide_permute(Lane& a, const WideLane& L) {
+__device__ __forceinline__ void wide_permute(uint32_t& a, const WideLane& L) {
 #pragma unroll
   for (int r = 0; r < 24; ++r) wide_round(a, L, r);
+  // iota of the last round (eqs. 8-9)
+  a ^= L.origin & (L.half ? kHalfRC.o[23] : kHalfRC.e[23]);
+}
+
+// This lane's half of the word (lo, hi): bits h, h + 2, ... gathered by
+// swapping neighbouring bits, pairs, nibbles and bytes.
+__device__ __forceinline__ uint32_t gather_half(uint32_t lo, uint32_t hi, uint32_t h) {
+  uint32_t t = ((lo >> h) & 0x55555555u) | (((hi >> h) & 0x55555555u) << 1);
+  uint32_t s;
+  s = (t ^ (t >> 1)) & 0x22222222u;
+  t ^= s ^ (s << 1);
+  s = (t ^ (t >> 2)) & 0x0C0C0C0Cu;
+  t ^= s ^ (s << 2);
+  s = (t ^ (t >> 4)) & 0x00F000F0u;
+  t ^= s ^ (s << 4);
+  return __builtin_amdgcn_perm(t, t, 0x03010200u);
+}
+
+// The reverse, for output: dword h (low or high) of this lane's word.
+__device__ __forceinline__ uint32_t output_dword(uint32_t a, const WideLane& L) {
+  const uint32_t other = read_lane(L.partner, a);
+  const uint32_t e = L.half ? other : a, o = L.half ? a : other;
+  // 16 even bits and 16 odd bits, then spread
+  uint32_t t = __builtin_amdgcn_perm(o, e, L.half ? 0x07060302u : 0x05040100u);
+  t = __builtin_amdgcn_perm(t, t, 0x03010200u);
+  uint32_t s;
+  s = (t ^ (t >> 4)) & 0x00F000F0u;
+  t ^= s ^ (s << 4);
+  s = (t ^ (t >> 2)) & 0x0C0C0C0Cu;
+  t ^= s ^ (s << 2);
+  s = (t ^ (t >> 1)) & 0x22222222u;
+  t ^= s ^ (s << 1);
+  return t;
 }
 
 // The dwords holding the bytes of this lane's word of the block at message
@@ -153,11 +227,11 @@ __device__ __forceinline__ void load_word(WordDw& d, const uint8_t* msg, uint32_
   }
 }
 
-// Xor this lane's word of one block into the state (eq. 12's P_i); on the
-// final block (`rem` message bytes left, rem < R) only message bytes are
+// Xor this lane's half of one block word into the state (eq. 12's P_i); on
+// the final block (`rem` message bytes left, rem < R) only message bytes are
 // kept and the suffix/pad10*1 bytes are added: `pad` at byte rem, 0x80 on
 // byte R - 1.
-__device__ __forceinline__ void absorb_word(Lane& a, const WordDw& d, uint32_t sh, int R, bool fin,
+__device__ __forceinline__ void absorb_word(uint32_t& a, const WordDw& d, uint32_t sh, int R, bool fin,
                                             uint32_t rem, uint32_t pad, const WideLane& L) {
   uint32_t lo = __builtin_amdgcn_alignbyte(d.w[1], d.w[0], sh);
   uint32_t hi = __builtin_amdgcn_alignbyte(d.w[2], d.w[1], sh);
@@ -169,21 +243,17 @@ __device__ __forceinline__ void absorb_word(Lane& a, const WordDw& d, uint32_t s
     if (v >= 4 && v < 8) hi ^= pad << (8 * (v - 4));
     if (8 * static_cast<int>(L.word) == R - 8) hi ^= 0x80000000u;
   }
-  if (8u * L.word < static_cast<uint32_t>(R)) {
-    a.lo ^= lo;
-    a.hi ^= hi;
-  }
+  const uint32_t half = gather_half(lo, hi, L.half);
+  if (8u * L.word < static_cast<uint32_t>(R)) a ^= half;
 }
 
 // The digest (Section 3.2, eq. 15): words 0 .. D/8 of the final state, each
-// written by the lane that holds it; with `slot_dw` = 16 (mixed form) the
+// written by the lanes that hold it; with `slot_dw` = 16 (mixed form) the
 // slot is filled with zeros past the digest.
-__device__ __forceinline__ void store_word(uint32_t* o, Lane a, int dw, int slot_dw, const WideLane& L) {
-  const int k = 2 * static_cast<int>(L.word);
-  if (L.word < 25u) {
-    if (k < slot_dw) o[k] = k < dw ? a.lo : 0u;
-    if (k + 1 < slot_dw) o[k + 1] = k + 1 < dw ? a.hi : 0u;
-  }
+__device__ __forceinline__ void store_word(uint32_t* o, uint32_t a, int dw, int slot_dw, const WideLane& L) {
+  const uint32_t v = output_dword(a, L);
+  const int k = 2 * static_cast<int>(L.word) + static_cast<int>(L.half);
+  if (L.word < 25u && k < slot_dw) o[k] = k < dw ? v : 0u;
 }
 
 }  // namespace wide

@@ -50,7 +50,7 @@ class KbError(RuntimeError):
 
 NB_CLASSES = 8
 STAGING_DEFAULT, STAGING_DIRECT, STAGING_PREFETCH = 0, 1, 2
-THREADS_WIDE = 32  # class_threads value of the wide split tail (32 lanes per state)
+THREADS_WIDE = 32  # class_threads value of the wide split tail (a wave per state)
 
 
 class Tile(ctypes.Structure):
