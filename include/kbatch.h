@@ -369,6 +369,15 @@ const char* keccak_server_last_error(void);
  * aligned, plus one digest); 0 for a variant out of range.  Host only. */
 uint64_t keccak_tree_workspace_bytes(int variant, uint64_t n_leaves);
 
+/*
+ * keccak_check_bounds -- whether every slice (offset, length) of a table lies
+ * inside data_bytes bytes (*inside = 1; a value of 2^63 or more counts as
+ * outside).  Waits for `stream` (one kernel, the answer in host memory), so it
+ * is refused on a capturing stream (KB_EINVAL).
+ */
+int keccak_check_bounds(const uint64_t* d_offsets, const uint64_t* d_lengths, uint64_t n,
+                        uint64_t data_bytes, hipStream_t stream, int* inside);
+
 /* Digest and rate sizes in bytes of a variant; -1 if it is out of range. */
 int keccak_digest_bytes(int variant);
 int keccak_rate_bytes(int variant);

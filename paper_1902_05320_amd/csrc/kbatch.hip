@@ -36,6 +36,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -1415,6 +1416,29 @@ __global__ void k_reset(uint32_t* __restrict__ meta, uint32_t words) {
     meta[k] = 0u;
 }
 
+// Bounds check of a slice table: a non-zero word at `bad` (host memory) if any
+// slice is negative as a signed number or ends past data_bytes.  One read of
+// the table, bound by memory; kCheckPer entries per thread keep a few loads in
+// flight and a batch of 2^24 at 8192 workgroups.
+constexpr uint32_t kCheckPer = 8;
+
+__global__ __launch_bounds__(kBlock) void k_check_bounds(const uint64_t* __restrict__ offs,
+                                                         const uint64_t* __restrict__ lens, uint64_t n,
+                                                         uint64_t data_bytes, uint32_t* bad) {
+  const uint64_t first = static_cast<uint64_t>(blockIdx.x) * (kBlock * kCheckPer) + threadIdx.x;
+  bool out = false;
+#pragma unroll
+  for (uint32_t k = 0; k < kCheckPer; ++k) {
+    const uint64_t i = first + k * kBlock;
+    if (i < n) {
+      const uint64_t o = offs[i], l = lens[i];
+      out = out || ((o | l) >> 63) != 0u || o + l > data_bytes;
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64(out) != 0 && (threadIdx.x & 63u) == 0u)
+    __hip_atomic_store(bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Count the dwords where two digest buffers differ (autotuner parity gate).
 __global__ __launch_bounds__(kBlock) void k_compare(const uint32_t* __restrict__ a,
                                                     const uint32_t* __restrict__ b, uint64_t words,
@@ -1590,6 +1614,46 @@ int get_ws(hipStream_t stream, uint64_t msgs, uint64_t tree_bytes, Workspace** o
   *out = &w;
   return KB_OK;
 }
+
+// Host words that k_check_bounds reports to, one per check under way (any
+// thread, any stream), kept for the next one: a pinned page of them at a time,
+// given back by keccak_release() when none is in use.
+struct CheckWords {
+  static constexpr int kPerPage = 64;  // a 64-byte line each
+  std::mutex mu;
+  std::vector<uint32_t*> pages, free;
+
+  uint32_t* take() {
+    std::lock_guard<std::mutex> lk(mu);
+    if (free.empty()) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kPerPage * 64, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      uint32_t* page = static_cast<uint32_t*>(p);
+      std::memset(page, 0, kPerPage * 64);
+      pages.push_back(page);
+      free.reserve(pages.size() * kPerPage);  // give() never allocates
+      for (int k = 0; k < kPerPage; ++k) free.push_back(page + 16 * k);
+    }
+    uint32_t* w = free.back();
+    free.pop_back();
+    return w;
+  }
+  void give(uint32_t* w) {
+    std::lock_guard<std::mutex> lk(mu);
+    free.push_back(w);
+  }
+  void release() {
+    std::lock_guard<std::mutex> lk(mu);
+    if (free.size() != pages.size() * kPerPage) return;
+    for (uint32_t* p : pages) (void)hipHostFree(p);
+    pages.clear();
+    free.clear();
+  }
+};
+CheckWords g_check;
 
 struct Batch {
   int variant;  // 0..3, kMixed, kShake128 or kShake256
@@ -2467,6 +2531,42 @@ uint64_t keccak_tree_workspace_bytes(int variant, uint64_t n_leaves) {
   return tree_workspace_bytes(n_leaves, kb::digest_bytes_of(variant));
 }
 
+int keccak_check_bounds(const uint64_t* d_offsets, const uint64_t* d_lengths, uint64_t n,
+                        uint64_t data_bytes, hipStream_t stream, int* inside) {
+  g_err.clear();
+  if (!inside) return fail(KB_EINVAL, "NULL output pointer");
+  *inside = 0;
+  if (n && (!d_offsets || !d_lengths)) return fail(KB_EINVAL, "NULL pointer with n > 0");
+  if (reinterpret_cast<uintptr_t>(d_offsets) % 8 || reinterpret_cast<uintptr_t>(d_lengths) % 8)
+    return fail(KB_EINVAL, "d_offsets and d_lengths must be 8-byte aligned");
+  if (n == 0) {
+    *inside = 1;
+    return KB_OK;
+  }
+  const uint64_t blocks = (n + kBlock * kCheckPer - 1) / (kBlock * kCheckPer);
+  if (blocks > 0x7FFFFFFFull) return fail(KB_EINVAL, "table too large for one launch");
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  KB_HIP(hipStreamIsCapturing(stream, &cs));
+  if (cs != hipStreamCaptureStatusNone)
+    return fail(KB_EINVAL, "the bounds check waits on the host and cannot be captured");
+  uint32_t* bad = nullptr;
+  try {
+    bad = g_check.take();
+  } catch (const std::bad_alloc&) {
+  }
+  if (!bad) return fail(KB_ENOMEM, "no host memory for the bounds check");
+  hipLaunchKernelGGL(k_check_bounds, dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, stream,
+                     d_offsets, d_lengths, n, data_bytes, bad);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  // (after an error the word stays taken: the kernel may still write it)
+  if (e != hipSuccess) return fail(KB_EHIP, "bounds check: %s", hipGetErrorString(e));
+  *inside = *static_cast<volatile uint32_t*>(bad) == 0u;
+  *bad = 0u;
+  g_check.give(bad);
+  return KB_OK;
+}
+
 int keccak_digest_bytes(int variant) {
   return variant >= 0 && variant <= 3 ? kb::digest_bytes_of(variant) : -1;
 }
@@ -2498,6 +2598,7 @@ int keccak_release(void) {
     }
   }
   g_ws.clear();
+  g_check.release();
   if (rc) fail(rc, "keccak_release: a device could not be synchronised");
   return rc;
 }

@@ -222,6 +222,23 @@ def test_bounds_checked_in_binding(kb):
         kb.merkle_root(1, data, 0)
 
 
+@pytest.mark.parametrize("n", [1, 255, 256, 2048, 2049, 5000])
+def test_bounds_check_finds_each_fault(kb, n):
+    # one bad slice at the first, a middle and the last entry, of each kind
+    import torch
+    data = torch.zeros(1000, dtype=torch.uint8, device="cuda")
+    lens0, offs0 = torch.full((n,), 10, dtype=torch.int64), torch.full((n,), 990, dtype=torch.int64)
+    _say("bounds check", n)
+    kb._check_bounds(data, offs0.cuda(), lens0.cuda())
+    for at in {0, n // 2, n - 1}:
+        for off, ln in ((991, 10), (990, 11), (-1, 5), (5, -1), (1001, 0), (1 << 62, 1)):
+            offs, lens = offs0.clone(), lens0.clone()
+            offs[at], lens[at] = off, ln
+            with pytest.raises(ValueError):
+                kb._check_bounds(data, offs.cuda(), lens.cuda())
+    kb._check_bounds(data, offs0.cuda(), lens0.cuda())
+
+
 def test_order_and_repeat_invariance(kb):
     import torch
     b = wl.uneven(30000, 4000, seed=9)
