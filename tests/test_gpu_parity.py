@@ -149,11 +149,12 @@ def test_persistent_split_tail(kb, o2, case):
     assert (got1 == o2.sha3_batch(256, v1.data, v1.offsets, v1.lengths)).all()
 
 
-@pytest.mark.parametrize("n", [2049, 65536, 65537])
+@pytest.mark.parametrize("n", [2048, 2049, 65536, 65537])
 def test_pair_items_at_their_bounds(kb, o2, n):
     # lengths around one and several whole blocks at every offset mod 16 (whole
-    # blocks load unaligned, 32 messages to a pair wave), and the largest batch
-    # that goes to pairs whole against the smallest that does not
+    # blocks load unaligned, 32 messages to a pair wave); the largest batch that
+    # is one wide launch, and the largest that goes to pairs whole, each against
+    # the smallest that does not
     rng = np.random.Generator(np.random.PCG64(90))
     edges = np.concatenate([[0, 1, 3, 5]] + [m * R + np.arange(-5, 6) for R in RATES for m in (1, 2, 5)])
     lens = rng.choice(edges, n)
