@@ -294,13 +294,11 @@ __device__ __forceinline__ void split_hash(const uint8_t* msg, uint64_t len, int
 // that lie in the rate, r bits of output per permutation, until out_len
 // bytes are out; the permutation between reads involves all eight lanes of
 // the group, which all take the same number of turns (out_len is the batch's).
-// Bytes are stored one by one unless out_len is a multiple of 4 and `out` is
-// 4-byte aligned.
+// (unaligned 4-byte stores, the last bytes one by one).
 template <int V>
 __device__ __forceinline__ void split_xof(Lane (&a)[5], uint8_t* out, uint64_t out_len,
                                           const kb::split::SplitLane& L) {
   constexpr uint32_t R = SpongeShape<V>::kMaxRate;
-  const bool words = (out_len & 3u) == 0 && (reinterpret_cast<uintptr_t>(out) & 3u) == 0;
   for (uint64_t done = 0;;) {
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
@@ -311,8 +309,8 @@ __device__ __forceinline__ void split_xof(Lane (&a)[5], uint8_t* out, uint64_t o
           const uint32_t v = h ? a[j].hi : a[j].lo;
           const uint64_t at = done + 8u * li + 4u * h;
           if (at < out_len) {
-            if (words) {
-              *reinterpret_cast<uint32_t*>(out + at) = v;
+            if (at + 4u <= out_len) {
+              *reinterpret_cast<kb::Word1*>(out + at) = v;
             } else {
               for (uint32_t q = 0; q < 4u && at + q < out_len; ++q)
                 out[at + q] = static_cast<uint8_t>(v >> (8u * q));
@@ -397,19 +395,18 @@ __device__ __forceinline__ void wide_absorb(uint32_t& a, const uint8_t* msg, uin
 
 // XOF squeeze in the wide form (Section 3.2): each lane writes a dword of its
 // word when that lies in the rate, r bits of output per permutation, until
-// out_len bytes are out.  Bytes are stored one by one unless out_len is a multiple of 4
-// and `out` is 4-byte aligned.
+// out_len bytes are out.  (Unaligned 4-byte stores, the last bytes one by
+// one.)
 template <int V>
 __device__ __forceinline__ void wide_xof(uint32_t& a, uint8_t* out, uint64_t out_len,
                                          const kb::wide::WideLane& L) {
   constexpr uint32_t R = SpongeShape<V>::kMaxRate;
-  const bool words = (out_len & 3u) == 0 && (reinterpret_cast<uintptr_t>(out) & 3u) == 0;
   for (uint64_t done = 0;;) {
     const uint32_t v = kb::wide::output_dword(a, L);
     const uint64_t at = done + 8u * L.word + 4u * L.half;
     if (8u * L.word < R && at < out_len) {
-      if (words) {
-        *reinterpret_cast<uint32_t*>(out + at) = v;
+      if (at + 4u <= out_len) {
+        *reinterpret_cast<kb::Word1*>(out + at) = v;
       } else {
         for (uint32_t q = 0; q < 4u && at + q < out_len; ++q)
           out[at + q] = static_cast<uint8_t>(v >> (8u * q));
@@ -488,14 +485,13 @@ template <int V>
 __device__ __forceinline__ void pair_xof(uint32_t (&a)[25], uint8_t* out, uint64_t out_len,
                                          uint32_t h, uint32_t hi) {
   constexpr uint32_t R = SpongeShape<V>::kMaxRate;
-  const bool words = (out_len & 3u) == 0 && (reinterpret_cast<uintptr_t>(out) & 3u) == 0;
   for (uint64_t done = 0;;) {
 #pragma unroll
     for (int i = 0; i < static_cast<int>(R / 8); ++i) {
       const uint64_t at = done + 8u * i + 4u * h;
       if (at < out_len) {
-        if (words) {
-          *reinterpret_cast<uint32_t*>(out + at) = a[i];
+        if (at + 4u <= out_len) {
+          *reinterpret_cast<kb::Word1*>(out + at) = a[i];
         } else {
           for (uint32_t q = 0; q < 4u && at + q < out_len; ++q)
             out[at + q] = static_cast<uint8_t>(a[i] >> (8u * q));

@@ -101,8 +101,6 @@ struct HalfDw {
   uint32_t w[4 * kQ];
 };
 
-typedef uint32_t Word1 __attribute__((aligned(1)));
-
 template <int V>
 __device__ __forceinline__ void load_halves(HalfDw<V>& d, const uint8_t* msg, uint64_t len,
                                             uint64_t boff, int R, uint32_t h) {

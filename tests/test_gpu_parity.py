@@ -437,3 +437,24 @@ def test_shake_xof(kb, o2, security, mode):
         for i in range(b.n):
             m = b.data[b.offsets[i]:b.offsets[i] + b.lengths[i]].tobytes()
             assert got[i].tobytes() == o2.shake(security, m, out_len), (out_len, i)
+
+
+@pytest.mark.parametrize("security", [128, 256])
+@pytest.mark.parametrize("out_len", [15, 16, 17, 167, 168, 169, 500, 1001])
+def test_shake_xof_in_both_passes(kb, o2, security, out_len):
+    # more messages than one wide launch takes: the first 2048 are one block
+    # long (hashed and squeezed by the first pass), the rest up to three (the
+    # second pass); outputs around 16-byte stores and one rate, odd row
+    # addresses for odd lengths
+    import torch
+    rng = np.random.Generator(np.random.PCG64(95))
+    lens = np.concatenate([rng.integers(0, 100, 2048), rng.integers(100, 400, 200)])
+    b = wl.explicit(lens, seed=96, gap=1, lead=3)
+    data, offs, lns, _ = _to_dev(b)
+    _say("shake both passes", security, out_len)
+    got = kb.keccak_batch_xof(security, data, offs, lns, out_len)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    for i in range(b.n):
+        m = b.data[b.offsets[i]:b.offsets[i] + b.lengths[i]].tobytes()
+        assert got[i].tobytes() == o2.shake(security, m, out_len), (out_len, i)
