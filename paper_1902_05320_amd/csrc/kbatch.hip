@@ -57,8 +57,6 @@ using kb::SpongeShape;
 namespace {
 
 constexpr int kBlock = 256;         // threads per workgroup of the hashing kernels
-constexpr int kTreeTop = 1024;      // nodes the workgroup that reduces a tree's last levels takes
-constexpr int kTreeTopThreads = 512;  // its threads: two nodes (one pair) each at its first level
 constexpr uint32_t kKeyBins = 4096;  // block-count buckets (4095 = "4095 or more")
 constexpr uint32_t kScatterChunks = 64;  // deferred 64-message chunks per scatter tile
 constexpr uint32_t kLine = 64;       // 32-bit words per 256-byte line
@@ -571,73 +569,55 @@ struct TreeLevels {
   uint64_t off[64];
 };
 
-// Workgroup w owns nodes [T w, T w + T) of level `first` and reduces them
-// `levels` levels.  first == 0: it also hashes those leaves (leaf i is
-// min(leaf_size, total - i * leaf_size) bytes at data + i * leaf_size).  Each
-// level is separated by a workgroup barrier, which also orders the global
+// Three kernels share the tree:
+//   k_leaf   the leaf digests of a tree of few leaves, in the wide or the pair
+//            form (a thread per leaf would leave SIMDs idle);
+//   k_tree   256 leaves or nodes per workgroup, one per thread, then some
+//            levels above them: the leaf launch of large trees, and the levels
+//            of more nodes than k_tree_up's workgroups take at once;
+//   k_tree_up  32 nodes per workgroup, a pair per wave in the wide form, five
+//            levels up with the nodes between them in LDS.
+//
+// k_tree: workgroup w owns nodes [256 w, 256 w + 256) of level `first` and
+// reduces them `levels` levels.  With hash_leaves it hashes those leaves first (leaf
+// i is min(leaf_size, total - i * leaf_size) bytes at data + i * leaf_size).
+// Each level is separated by a workgroup barrier, which also orders the global
 // node writes of one level before the reads of the next.  The node of level
 // `top` (the root) is written to `root`.
 //
 // A level with more pairs per workgroup than the workgroup has 8-lane groups
-// hashes one pair per thread; the narrower levels at the top of each
-// workgroup's subtree, where one thread per pair would leave a wave's worth
-// of permutation latency for a handful of lanes, hash one pair per group in
-// the lane-split form (five lanes per state, about twice as fast per
-// permutation), and the levels of at most one pair per wave in the wide form
-// (half a state word per lane, about four times as fast).  The exchange
-// areas reuse the staging rows, which no level uses after the first split
-// one.
-//
-// A workgroup owns NODES nodes of level `first`: T for the leaf and middle
-// launches (one leaf or node per thread), 2T for the last workgroup, whose
-// first level is then one pair per thread (a 512-thread workgroup keeps the
-// 256-VGPR limit, where 1024 threads would cap it at 128 and spill).
-//
-// With W8 every message the kernel hashes is whole 8-byte words at an
-// 8-byte-aligned address (the host checks the leaves; node pairs always are):
-// blocks go from HBM into a per-wave LDS area with the loads that write LDS
-// directly, the next block's while the current one is permuted, and come back
-// as whole words (no byte realignment, no registers holding bytes in flight).
-template <int V, int T, bool PF, bool W8, int NODES = T, bool WL = false>
-__global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, uint64_t total,
-                                            uint64_t leaf_size, uint8_t* __restrict__ nodes,
-                                            uint8_t* __restrict__ root, int first, int levels,
-                                            int top, TreeLevels lv) {
+// hashes one pair per thread; the narrower ones, where one thread per pair
+// would leave a wave's worth of permutation latency for a handful of lanes,
+// hash one pair per group in the lane-split form (five lanes per state, about
+// twice as fast per permutation).  The exchange areas reuse the staging rows,
+// which no level uses after the first split one.
+// (The leaves were once loaded straight to LDS where they are whole aligned
+// words; with whole blocks loaded into registers that is the slower way, 825
+// against 819 us for 1 GiB of 4 KiB leaves.)
+template <int V>
+__global__ __launch_bounds__(kBlock) void k_tree(const uint8_t* __restrict__ data, uint64_t total,
+                                                 uint64_t leaf_size, uint8_t* __restrict__ nodes,
+                                                 uint8_t* __restrict__ root, bool hash_leaves, int first,
+                                                 int levels, int top, TreeLevels lv) {
   namespace sp = kb::split;
   using S = SpongeShape<V>;
   constexpr uint64_t D = kb::digest_bytes_of(V);
+  constexpr int T = kBlock;
   constexpr int kGroups = T / sp::kGroupLanes;
-  // SHA3-512's leaf kernel fits four waves per SIMD (125 VGPRs) only without
+  // SHA3-512's leaf kernel fits four waves per SIMD (116 VGPRs) only without
   // the split path (148), and its leaves are the long chains, so there the
   // in-workgroup levels stay one pair per thread.
-  constexpr bool kSplitLevels = !(V == 3 && T == kBlock);
+  constexpr bool kSplitLevels = V != 3;
   constexpr int kSplitDw = 2 * (kGroups * sp::kGroupSlots + 1);
-  constexpr int kWordsDw = (T / 64) * kb::WordArea<V>::kDw;
-  constexpr int kStageDw = W8 ? kWordsDw : T * S::kRowDw;
-  __shared__ __align__(16) uint32_t lds[kStageDw > kSplitDw ? kStageDw : kSplitDw];
+  __shared__ __align__(16) uint32_t lds[T * S::kRowDw];
   static_assert(kSplitDw <= T * S::kRowDw, "the split exchange area fits in the staging rows");
-  constexpr uint32_t kWaves = T / kb::wide::kStateLanes;
-  uint32_t* row = lds + (W8 ? 0u : threadIdx.x * S::kRowDw);
-  // one message of whole words (W8: through this wave's LDS area) or of any
-  // bytes (staged through this thread's row)
-  auto hash = [&](Lane (&A)[25], const uint8_t* msg, uint64_t len) {
-    if constexpr (W8)
-      kb::sponge_hash_words<V, PF>(
-          A, msg, len,
-          (__attribute__((address_space(3))) uint32_t*)(lds) +
-              __builtin_amdgcn_readfirstlane(threadIdx.x / 64u) * kb::WordArea<V>::kDw,
-          threadIdx.x & 63u);
-    else
-      kb::sponge_hash<V, PF>(A, msg, len, V, row);
-  };
+  uint32_t* row = lds + threadIdx.x * S::kRowDw;
+  auto hash = [&](Lane (&A)[25], const uint8_t* msg, uint64_t len) { kb::sponge_hash<V>(A, msg, len, V, row); };
   const uint64_t w = blockIdx.x;
   auto dst_of = [&](int level, uint64_t j) -> uint8_t* {
     return level == top ? root : nodes + lv.off[level] + j * D;
   };
-  static_assert(NODES == T || NODES == 2 * T, "one or two nodes per thread");
-  kb::wide::WideLane wide_lane;
-  if constexpr (WL) kb::wide::setup(wide_lane, threadIdx.x & 63u);
-  if (NODES == T && first == 0) {  // leaves: only launches with one node per thread take level 0
+  if (hash_leaves) {
     const uint64_t i = w * T + threadIdx.x;
     if (i < lv.m[0]) {
       const uint64_t off = i * leaf_size;
@@ -650,26 +630,8 @@ __global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, ui
   for (int k = 0; k < levels; ++k) {
     const int l = first + k;  // reading level l, writing level l + 1
     __syncthreads();
-    const uint64_t span = static_cast<uint64_t>(NODES) >> (k + 1);  // pairs of this workgroup
-    if (WL && span <= kWaves) {
-      // one pair per wave in the wide form
-      namespace wd = kb::wide;
-      const uint32_t lane = threadIdx.x & 63u;
-      const uint32_t p = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
-      const uint64_t j = w * span + p;
-      if (p < span && j < lv.m[l + 1]) {
-        const uint8_t* src = nodes + lv.off[l] + 2 * j * D;
-        uint32_t* d32 = reinterpret_cast<uint32_t*>(dst_of(l + 1, j));
-        if (2 * j + 1 < lv.m[l]) {
-          uint32_t a;
-          wide_absorb<V>(a, src, 2 * D, V, wide_lane);
-          wd::store_word(d32, a, static_cast<int>(D / 4), static_cast<int>(D / 4), wide_lane);
-        } else {
-          const uint32_t* s32 = reinterpret_cast<const uint32_t*>(src);
-          if (lane < D / 4) d32[lane] = s32[lane];
-        }
-      }
-    } else if (!kSplitLevels || span > static_cast<uint64_t>(kGroups)) {
+    const uint64_t span = static_cast<uint64_t>(T) >> (k + 1);  // pairs of this workgroup
+    if (!kSplitLevels || span > static_cast<uint64_t>(kGroups)) {
       const uint64_t j = w * span + threadIdx.x;
       if (threadIdx.x < span && j < lv.m[l + 1]) {
         const uint8_t* src = nodes + lv.off[l] + 2 * j * D;
@@ -705,6 +667,100 @@ __global__ __launch_bounds__(T) void k_tree(const uint8_t* __restrict__ data, ui
         }
       }
     }
+  }
+}
+
+// Leaf digests of a tree of few leaves, to `out` (level 0 of the nodes, or the
+// root of a one-leaf tree): PAIR false, a wave per leaf in the wide form; true,
+// two lanes per leaf.  One wave per workgroup, as in those forms' launches.
+template <int V, bool PAIR>
+__global__ __launch_bounds__(64) void k_leaf(const uint8_t* __restrict__ data, uint64_t total,
+                                             uint64_t leaf_size, uint64_t leaves,
+                                             uint8_t* __restrict__ out) {
+  constexpr uint64_t D = kb::digest_bytes_of(V);
+  constexpr int kDw = static_cast<int>(D / 4);
+  auto length = [&](uint64_t i) { return total - i * leaf_size < leaf_size ? total - i * leaf_size : leaf_size; };
+  if constexpr (PAIR) {
+    const uint32_t h = threadIdx.x % kb::pair::kPairLanes, hi = h ? ~0u : 0u;
+    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kPairStates + threadIdx.x / kb::pair::kPairLanes;
+    if (i >= leaves) return;
+    uint32_t a[25];
+    pair_absorb<V>(a, data + i * leaf_size, length(i), V, h, hi);
+    kb::pair::store_halves(reinterpret_cast<uint32_t*>(out + i * D), a, kDw, kDw, h);
+  } else {
+    const uint64_t i = blockIdx.x;
+    kb::wide::WideLane L;
+    kb::wide::setup(L, threadIdx.x);
+    uint32_t a;
+    wide_absorb<V>(a, data + i * leaf_size, length(i), V, L);
+    kb::wide::store_word(reinterpret_cast<uint32_t*>(out + i * D), a, kDw, kDw, L);
+  }
+}
+
+// Workgroup w reduces nodes [32 w, 32 w + 32) of level `first` up `levels` (at
+// most five) levels, one pair per wave in the wide form.  What bounds it is
+// the latency of one permutation a level: 4.5 us with 16 pairs (four waves per
+// SIMD), 2.9 with eight, 2.2 below.  The nodes between the levels stay in LDS:
+// through global memory every level waited for its stores and loads as well,
+// and one workgroup of 512 threads that took 512 nodes to the root (one pair
+// per thread, then five-lane, then wide) needed 73 us.
+constexpr int kUpNodes = 32;
+constexpr int kUpLevels = 5;
+constexpr int kUpThreads = kUpNodes / 2 * kb::wide::kStateLanes;
+
+template <int V>
+__global__ __launch_bounds__(kUpThreads) void k_tree_up(uint8_t* __restrict__ nodes,
+                                                        uint8_t* __restrict__ root, int first,
+                                                        int levels, int top, TreeLevels lv) {
+  namespace wd = kb::wide;
+  constexpr uint32_t D = kb::digest_bytes_of(V), DW = D / 4;
+  constexpr uint32_t RW = kb::rate_bytes_of(V) / 8, kWords = 2 * D / 8;  // words of a block, of a pair
+  static_assert(2 * D % 8 == 0 && kWords / RW < 2, "a pair is whole words, one or two blocks");
+  constexpr uint32_t kBlocks = kWords / RW + 1;
+  __shared__ uint32_t between[2][kUpNodes / 2 * DW];
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t p = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);  // this wave's pair
+  wd::WideLane L;
+  wd::setup(L, lane);
+  for (int k = 0; k < levels; ++k) {
+    const int l = first + k;  // reading level l, writing level l + 1
+    const uint32_t span = kUpNodes >> (k + 1);
+    const uint64_t j = static_cast<uint64_t>(blockIdx.x) * span + p;
+    if (p < span && j < lv.m[l + 1]) {
+      const uint32_t* above = reinterpret_cast<const uint32_t*>(nodes + lv.off[l] + 2 * j * D);
+      const uint32_t* inside = between[(k + 1) & 1] + 2 * p * DW;
+      auto node_dword = [&](uint32_t i) { return k == 0 ? above[i] : inside[i]; };
+      const bool paired = 2 * j + 1 < lv.m[l];  // else the last node is carried up
+      uint32_t v = 0u;
+      if (paired) {
+        uint32_t a = 0u;
+#pragma unroll
+        for (uint32_t b = 0; b < kBlocks; ++b) {
+          const uint32_t m = b * RW + L.word;  // word of the pair's message
+          uint32_t lo = 0u, hi = 0u;
+          if (L.word < RW) {
+            if (m < kWords) {
+              lo = node_dword(2 * m);
+              hi = node_dword(2 * m + 1);
+            }
+            if (m == kWords) lo = SpongeShape<V>::kPadByte;
+            if (b + 1 == kBlocks && L.word == RW - 1) hi ^= 0x80000000u;
+          }
+          a ^= wd::gather_half(lo, hi, L.half);
+          wd::wide_permute(a, L);
+        }
+        v = wd::output_dword(a, L);
+      }
+      const uint32_t q = paired ? 2 * L.word + L.half : lane;  // dword of the digest this lane has
+      if (q < DW && (!paired || L.word < 25u)) {
+        if (!paired) v = node_dword(q);
+        if (k + 1 < levels)
+          between[k & 1][p * DW + q] = v;
+        else
+          reinterpret_cast<uint32_t*>(l + 1 == top ? root : nodes + lv.off[l + 1] + j * D)[q] = v;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -2001,52 +2057,54 @@ int merkle_impl(const uint8_t* data, uint64_t total, uint64_t leaf, uint8_t* roo
   constexpr uint64_t D = kb::digest_bytes_of(V);
   TreeLevels lv;
   const int L = tree_levels(total ? (total + leaf - 1) / leaf : 1, D, lv);  // levels above the leaves
-  // leaves of whole 8-byte words at 8-byte-aligned addresses take the W8 kernel
-  const bool w8 = leaf % 8u == 0 && total % 8u == 0 && reinterpret_cast<uintptr_t>(data) % 8u == 0;
   Workspace* w = own;
   int rc = own ? KB_OK : get_ws(s, 0, lv.off[L] + D, &w);
   if (rc) return rc;
-  // The leaves and the first level in 256-thread workgroups, then launches of
-  // up to 8 levels while over kTreeTop nodes remain, then one workgroup of
-  // kTreeTopThreads threads reduces the rest.  The root is written by
-  // whichever launch produces level L (the leaf launch itself for one or two
-  // leaves).  A leaf workgroup that went on with its narrow levels would hold
-  // its CU slot while few lanes work: one level there measured about 1 %
-  // faster per root than eight.
-  int first = 0;
-  do {
-    if (first == 0 || lv.m[first] > static_cast<uint64_t>(kTreeTop)) {
-      const int cap = first == 0 ? 1 : 8;
-      const int levels = L - first < cap ? L - first : cap;
-      const uint64_t blocks = (lv.m[first] + kBlock - 1) / kBlock;
-      {
-        TimedLaunch tl(s, KB_KERNEL_TREE);
-        if (first > 0)
-          hipLaunchKernelGGL((k_tree<V, kBlock, kb::kPrefetch<V>, true, kBlock, true>),
-                             dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, s, data, total,
-                             leaf, w->tree, root, first, levels, L, lv);
-        else if (w8)
-          hipLaunchKernelGGL((k_tree<V, kBlock, kb::kPrefetch<V>, true>),
-                             dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, s, data, total,
-                             leaf, w->tree, root, first, levels, L, lv);
-        else
-          hipLaunchKernelGGL((k_tree<V, kBlock, kb::kPrefetch<V>, false>),
-                             dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, s, data, total,
-                             leaf, w->tree, root, first, levels, L, lv);
-      }
-      KB_HIP(hipGetLastError());
-      first += levels;
+  int dev = 0, cus = 0;
+  KB_HIP(hipGetDevice(&dev));
+  if ((rc = cu_count(dev, &cus))) return rc;
+  const uint64_t leaves = lv.m[0], simds = 4u * static_cast<uint64_t>(cus);
+  int first = 0;  // the lowest level whose nodes are there
+  {
+    TimedLaunch tl(s, KB_KERNEL_TREE);
+    uint8_t* const out = L == 0 ? root : w->tree;
+    if (leaves <= 2u * simds) {
+      // at most two waves per SIMD in the wide form: 2.2-2.9 us per block
+      hipLaunchKernelGGL((k_leaf<V, false>), dim3(static_cast<uint32_t>(leaves)), dim3(64), 0, s, data,
+                         total, leaf, leaves, out);
+    } else if (leaves <= 2u * kPairStates * simds) {
+      // at most two waves per SIMD in the pair form: 5.5-8 us per block, where
+      // one thread per leaf takes 8.8-9.6
+      hipLaunchKernelGGL((k_leaf<V, true>), dim3(static_cast<uint32_t>((leaves + kPairStates - 1) / kPairStates)),
+                         dim3(64), 0, s, data, total, leaf, leaves, out);
     } else {
-      {
-        TimedLaunch tl(s, KB_KERNEL_TREE);
-        hipLaunchKernelGGL((k_tree<V, kTreeTopThreads, false, true, kTreeTop, true>), dim3(1),
-                           dim3(kTreeTopThreads), 0, s, data, total, leaf, w->tree, root, first,
-                           L - first, L, lv);
-      }
-      KB_HIP(hipGetLastError());
-      first = L;
+      // one thread per leaf, and one level: a leaf workgroup that went on with
+      // narrow levels would hold its CU slot while few lanes work
+      first = L < 1 ? L : 1;
+      const uint64_t blocks = (leaves + kBlock - 1) / kBlock;
+      hipLaunchKernelGGL(k_tree<V>, dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, s, data, total,
+                         leaf, w->tree, root, true, 0, first, L, lv);
     }
-  } while (first < L);
+  }
+  KB_HIP(hipGetLastError());
+  const uint64_t up_nodes = static_cast<uint64_t>(kUpNodes) * cus;  // a workgroup of k_tree_up per CU
+  while (first < L) {
+    TimedLaunch tl(s, KB_KERNEL_TREE);
+    int levels = 1;
+    if (lv.m[first] > up_nodes) {
+      while (levels < 8 && lv.m[first + levels] > up_nodes) ++levels;
+      const uint64_t blocks = (lv.m[first] + kBlock - 1) / kBlock;
+      hipLaunchKernelGGL(k_tree<V>, dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, s, data, total,
+                         leaf, w->tree, root, false, first, levels, L, lv);
+    } else {
+      levels = L - first < kUpLevels ? L - first : kUpLevels;
+      const uint64_t blocks = (lv.m[first] + kUpNodes - 1) / kUpNodes;
+      hipLaunchKernelGGL(k_tree_up<V>, dim3(static_cast<uint32_t>(blocks)), dim3(kUpThreads), 0, s, w->tree,
+                         root, first, levels, L, lv);
+    }
+    KB_HIP(hipGetLastError());
+    first += levels;
+  }
   return KB_OK;
 }
 

@@ -458,3 +458,19 @@ def test_shake_xof_in_both_passes(kb, o2, security, out_len):
     for i in range(b.n):
         m = b.data[b.offsets[i]:b.offsets[i] + b.lengths[i]].tobytes()
         assert got[i].tobytes() == o2.shake(security, m, out_len), (out_len, i)
+
+
+@pytest.mark.parametrize("v", [0, 1, 2, 3])
+def test_merkle_forms_at_their_bounds(kb, o2, v):
+    # leaf counts around what the wide leaves (2048), one workgroup of the upper
+    # levels per CU (8192 nodes) and the pair leaves (65536) take, and around
+    # the upper kernel's 32 nodes a workgroup and 1024 in two launches
+    import torch
+    rng = np.random.Generator(np.random.PCG64(110 + v))
+    for n_leaves in (31, 32, 33, 1023, 1025, 2048, 2049, 8191, 8193, 16385, 65536, 65537):
+        leaf, cut = (9, 4) if n_leaves % 2 else (RATES[v] + 8, 0)
+        data = rng.integers(0, 256, n_leaves * leaf - cut, dtype=np.uint8)
+        _say("merkle forms", v, n_leaves, leaf, data.size)
+        got = kb.merkle_root(v, torch.from_numpy(data).cuda(), leaf)
+        torch.cuda.synchronize()
+        assert got.cpu().numpy().tobytes() == o2.merkle_root(8 * DIGEST[v], data, leaf)
