@@ -82,38 +82,27 @@ __device__ void rounds_narrow(uint32_t (&A)[25], int ir0, int nr) {
   }
 }
 
-// n_r rounds from i_r = ir0 on 64-bit lanes.
-__device__ void rounds_wide(kb::Lane (&A)[25], int ir0, int nr) {
-  for (int k = 0; k < nr; ++k) {
-    kb::Lane C[5], B[25];
-#pragma unroll
-    for (int x = 0; x < 5; ++x) {
-      C[x].lo = kb::xor3(kb::xor3(A[x].lo, A[x + 5].lo, A[x + 10].lo), A[x + 15].lo, A[x + 20].lo);
-      C[x].hi = kb::xor3(kb::xor3(A[x].hi, A[x + 5].hi, A[x + 10].hi), A[x + 15].hi, A[x + 20].hi);
-    }
-#pragma unroll
-    for (int x = 0; x < 5; ++x) {
-      const kb::Lane r = kb::rotl(C[(x + 1) % 5], 1);
-#pragma unroll
-      for (int y = 0; y < 5; ++y) {
-        A[x + 5 * y].lo = kb::xor3(A[x + 5 * y].lo, C[(x + 4) % 5].lo, r.lo);
-        A[x + 5 * y].hi = kb::xor3(A[x + 5 * y].hi, C[(x + 4) % 5].hi, r.hi);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 25; ++i) B[kb::kMaps.dst[i]] = kb::rotl(A[i], kb::kMaps.rot[i]);
-#pragma unroll
-    for (int y = 0; y < 5; ++y)
-#pragma unroll
-      for (int x = 0; x < 5; ++x) {
-        const kb::Lane a = B[x + 5 * y], b = B[(x + 1) % 5 + 5 * y], c = B[(x + 2) % 5 + 5 * y];
-        A[x + 5 * y].lo = a.lo ^ (~b.lo & c.lo);
-        A[x + 5 * y].hi = a.hi ^ (~b.hi & c.hi);
-      }
-    const int i = rc_index(ir0 + k);
-    A[0].lo ^= kRCAll.lo[i];
-    A[0].hi ^= kRCAll.hi[i];
+// n_r rounds from i_r = ir0 on 64-bit lanes: the SHA-3 path's round, in phases.
+// 2^20 states of 24 rounds: 130 us, 136 with the instructions of a round mixed
+// and one round per iteration.  (The rounds alone take 84 us at the
+// register-held rate, 420 MB 82 us at a copy's.  Going through LDS so that
+// global memory sees whole lines: 147, three waves per SIMD instead of five.)
+__device__ __forceinline__ void rounds_wide(kb::Lane (&A)[25], int ir0, int nr) {
+  int i = rc_index(ir0);
+  auto round = [&]() {
+    kb::keccak_round_rc(A, kRCAll.lo[i], kRCAll.hi[i]);
+    i = i == 254 ? 0 : i + 1;
+  };
+  int k = 0;
+#pragma unroll 1
+  for (; k + 4 <= nr; k += 4) {
+    round();
+    round();
+    round();
+    round();
   }
+#pragma unroll 1
+  for (; k < nr; ++k) round();
 }
 
 constexpr int kThreads = 256;

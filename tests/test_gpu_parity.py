@@ -474,3 +474,20 @@ def test_merkle_forms_at_their_bounds(kb, o2, v):
         got = kb.merkle_root(v, torch.from_numpy(data).cuda(), leaf)
         torch.cuda.synchronize()
         assert got.cpu().numpy().tobytes() == o2.merkle_root(8 * DIGEST[v], data, leaf)
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 257])
+def test_keccak_p_1600_wave_edges(kb, o2, n):
+    # counts around a wave and a workgroup; the states start one byte past an
+    # aligned address, with canaries around; 24 rounds are six turns of four
+    import torch
+    rng = np.random.Generator(np.random.PCG64(120))
+    raw = rng.integers(0, 256, 1 + 200 * n + 64, dtype=np.uint8)
+    d = torch.from_numpy(raw.copy()).cuda()
+    _say("keccak_p 1600 edges", n)
+    kb.keccak_p_batch(1600, 24, d[1:1 + 200 * n].view(n, 200))
+    got = d.cpu().numpy()
+    assert got[0] == raw[0] and (got[1 + 200 * n:] == raw[1 + 200 * n:]).all()
+    for s in range(n):
+        at = slice(1 + 200 * s, 201 + 200 * s)
+        assert got[at].tobytes() == o2.keccak_f1600(raw[at].tobytes()), s
