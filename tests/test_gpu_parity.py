@@ -149,12 +149,12 @@ def test_persistent_split_tail(kb, o2, case):
     assert (got1 == o2.sha3_batch(256, v1.data, v1.offsets, v1.lengths)).all()
 
 
-@pytest.mark.parametrize("n", [2048, 2049, 65536, 65537])
+@pytest.mark.parametrize("n", [2048, 2049, 4096, 4097, 65536, 65537])
 def test_pair_items_at_their_bounds(kb, o2, n):
     # lengths around one and several whole blocks at every offset mod 16 (whole
-    # blocks load unaligned, 32 messages to a pair wave); the largest batch that
-    # is one wide launch, and the largest that goes to pairs whole, each against
-    # the smallest that does not
+    # blocks load unaligned, 32 messages to a pair wave); the largest batches
+    # that are one wide launch, whose first pass is wide, and that go to pairs
+    # whole, each against the smallest that is not
     rng = np.random.Generator(np.random.PCG64(90))
     edges = np.concatenate([[0, 1, 3, 5]] + [m * R + np.arange(-5, 6) for R in RATES for m in (1, 2, 5)])
     lens = rng.choice(edges, n)
@@ -442,13 +442,13 @@ def test_shake_xof(kb, o2, security, mode):
 @pytest.mark.parametrize("security", [128, 256])
 @pytest.mark.parametrize("out_len", [15, 16, 17, 167, 168, 169, 500, 1001])
 def test_shake_xof_in_both_passes(kb, o2, security, out_len):
-    # more messages than one wide launch takes: the first 2048 are one block
+    # more messages than a wide first pass takes: the first 4096 are one block
     # long (hashed and squeezed by the first pass), the rest up to three (the
     # second pass); outputs around 16-byte stores and one rate, odd row
     # addresses for odd lengths
     import torch
     rng = np.random.Generator(np.random.PCG64(95))
-    lens = np.concatenate([rng.integers(0, 100, 2048), rng.integers(100, 400, 200)])
+    lens = np.concatenate([rng.integers(0, 100, 4096), rng.integers(100, 400, 200)])
     b = wl.explicit(lens, seed=96, gap=1, lead=3)
     data, offs, lns, _ = _to_dev(b)
     _say("shake both passes", security, out_len)
