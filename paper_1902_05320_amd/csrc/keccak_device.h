@@ -117,9 +117,10 @@ __device__ __forceinline__ Lane rotl(Lane v, int n) {
 // (theta's 10, rho's 48), and a wave raises its priority for a run of rotations and
 // drops it for the simple ones: rotations are got out of the way first and the
 // waves left are all at simple instructions and pair.  Register-held states,
-// 3 waves per SIMD: 9.0 -> 12.85 G permutations/s, at 0.39 instructions per
-// SIMD and cycle (the mix allows 0.377 with every pair used and 4-cycle
-// rotations; the clock falls from 2.38 to 2.16 GHz at that power).  Raised for
+// 3 waves per SIMD: 9.0 -> 12.85 G permutations/s, 0.25 -> 0.39 instructions
+// per SIMD and cycle (all simple ones paired and four cycles a rotation would
+// be 0.377, so a few rotations pair as well); the clock falls from 2.38 to
+// 2.16 GHz at that power, which is the limit now.  Raised for
 // rho alone 10.8, from theta's rotations to the end of rho 11.9; phases with
 // no priorities 9.0.  In the kernels: 2^24 x 64 B 1.62 -> 1.30 ms, the 1 GiB
 // tree of 4 KiB leaves 1.01 -> 0.85 ms, 100003 x 1001 B SHA3-384 0.41 -> 0.35.
