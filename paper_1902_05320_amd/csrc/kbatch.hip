@@ -68,9 +68,10 @@ enum : int {
   CTL_ITEM_TILES = 2,
   CTL_NDEF_CHUNKS = 3,  // chunks the first pass deferred
   CTL_MAXKEY = 4,       // largest block-count key deferred
-  CTL_SPLIT_WAVES = 5,  // waves per SIMD that take them
+  CTL_SPLIT_WAVES = 5,  // waves per SIMD that take split items
   CTL_SPLIT_N = 6,      // bucketed order positions [0, CTL_SPLIT_N) are hashed in the wide split form
   CTL_PAIR_KEY = 7,     // items of at least this many blocks are hashed in the pair form
+  CTL_FRONT = 10,       // the wave of a SIMD (in order of arrival) that takes items from the front
   CTL_USEFUL = 8,       // uint64 (words 8, 9): block counts of the deferred messages
   CTL_DPREFIX = 16,     // words 16..24: exclusive prefix of the deferred sub-list lengths
   CTL_WORDS = 64
@@ -84,7 +85,7 @@ enum : uint32_t {
 
 // One word per SIMD of the chip, indexed from the wave's hardware id (XCC,
 // shader engine, shader array, CU, SIMD): the waves that have arrived there.
-// The first one takes queue items from the front.
+// One of them (CTL_FRONT) takes queue items from the front.
 constexpr uint32_t kSimdSlots = 8 * 8 * 2 * 16 * 4;
 
 // The queue is dealt round-robin into kQueues sub-queues (item t goes to
@@ -144,6 +145,7 @@ struct PassArgs {
   uint32_t* order;      // bucketed order of the deferred messages, n entries
   WorkItem* items;      // queue items, max_items(n) entries
   uint32_t steps;       // permutations per lane in one queue item
+  uint32_t simds;       // SIMDs of the chip
   uint32_t pair_cap;    // past the split tail, at most this many messages go to the pair form all
   uint32_t split_cap;   // most messages the split tail may take (SHA-3 variants)
   // Per block-count class c, packed so that no array is indexed at run time
@@ -899,38 +901,50 @@ constexpr uint32_t kRanksPerThread = kKeyBins / kBlock;
 
 // The first CTL_SPLIT_N positions of the bucketed order (the longest
 // messages) go to the split form: the messages of at least
-// max(kSplitMinKey, 2 x the blocks per resident lane) blocks, at most
-// `split_cap` of them (twice that when every deferred message qualifies).
-// Below the second bound the batch's throughput, not
-// its longest chain, sets the time, and a split item (one message per wave)
-// costs throughput.  (An earlier bound of 4 x the mean block count kept a
-// batch of a few equal long messages out of the split form: 8 x 64 KiB ran
-// at 11.0 us per block of the chain, now 3.8.)
+// max(kSplitMinKey, kSplitHalves / 2 x the share of a SIMD) blocks, at most
+// `split_cap` of them (twice that when every deferred message qualifies).  A
+// SIMD's share is the batch's blocks over 64 lanes of every SIMD: hashed one
+// thread per message it takes some 5.3 us a block, so below the second bound
+// the pair form (7 us a block of the chain) ends before or soon after the rest
+// of the batch, and a split item (one message per wave) costs throughput.
+// Mixed messages of 0 .. 16 KiB, all lengths as likely, 10^5 of them: bound
+// 2/2 or 3/2 2.47 ms, 4/2 and 5/2 1.79; 65537 SHA3-512 1.98, 2.01, 1.90, 1.54
+// (2/2 .. 5/2).  2^18 log-uniform SHA3-512 of 0 .. 16 KiB 1.92, 1.90, 1.90, 1.46.
 constexpr uint32_t kSplitMinKey = 32;
+constexpr uint64_t kSplitHalves = 5;
 
 // Past the split range, the pair form (two lanes per message) takes
 //   - every message, if they are at most two pair waves per SIMD (64 K on 1024
-//     SIMDs): there the one-thread form would leave lanes idle and each chain
-//     runs at one thread's speed.  32768 x 4 KiB SHA3-256: 313 us with one
-//     thread per message, 247 with pairs (6.9 us per block of the chain
-//     against 8.9); at 65536 messages 8.6 against 9.6, at 131072 pairs are the
-//     slower form (15.2 against 13.8);
-//   - of a deep batch (two messages per resident lane and more), those of at
-//     least kPairDeepEighths / 8 x the blocks per resident lane: in the time
-//     that takes a wave that shares its SIMD, the whole batch is hashed, so
-//     these chains would end last.  2^20 uneven messages: no pairs 2.45-2.49
-//     ms, from 9/8 2.29, 11/8 2.13, 12/8 2.12, 13/8 2.31.  (A SIMD left to the
-//     one long item instead gained nothing: 2.36.)
-// Between the two (one item or so per wave) one thread per message keeps the
-// waves of a SIMD at two: 100003 x 1001 B SHA3-384 291 us, 320 with pairs.
+//     SIMDs), and no more than the waves that take no split items: there the
+//     one-thread form would leave lanes idle and each chain runs at one
+//     thread's speed.  32768 x 4 KiB SHA3-256: 313 us with one thread per
+//     message, 247 with pairs (6.9 us per block of the chain against 8.9); at
+//     65536 messages 8.6 against 9.6, at 131072 pairs are the slower form
+//     (15.2 against 13.8).  50000 mixed messages, all lengths to 16 KiB as
+//     likely, beside a split tail: 2.03 ms all in pairs (1563 items, the mixed
+//     kernel has 1024 other waves), 1.61 by the next rule;
+//   - else those of at least kPairDeepEighths / 8 x the mean blocks per message,
+//     or per lane where two waves per SIMD hold fewer lanes than messages: in
+//     the time that takes a wave that shares its SIMD, the whole batch is
+//     hashed, so these chains would end last.  2^20 uneven messages: no pairs
+//     2.45-2.49 ms, from 9/8 2.29, 11/8 2.13, 12/8 2.12, 13/8 2.31.  (A SIMD
+//     left to the one long item instead gained nothing: 2.36.)  10^5 mixed
+//     messages of up to 16 KiB, log-uniform: no pairs 1.31 ms, 12/8 1.16.
+// A batch of equal messages above the first bound has none of these: one
+// thread per message keeps the waves of a SIMD at two (100003 x 1001 B
+// SHA3-384 291 us, 320 with pairs).
 constexpr uint64_t kPairDeepEighths = 12;
 // Wide split items (messages) per SIMD.  A SIMD's front wave takes them one
-// after the other, unless the middle one is longer than 3/5 of the longest:
-// then a second wave takes its share at the same time.  Alone on its SIMD a
-// chain runs at 2.4 us per block, two share it at 2.9-3.4, so the second wave
-// pays where two of the items in turn would outlast the longest one.  2048 x
-// 16 KiB 3.4 us per block of the chain with two waves, 5.3 with one; the
-// serving burst, whose lengths spread over decades, 2.55 ms against 2.17-2.50.
+// after the other, unless the middle one is longer than 3/5 of the longest and
+// no message past the split range is longer than a quarter of it: then a second
+// wave takes its share at the same time.  Alone on its SIMD a chain runs at 2.4
+// us per block, two share it at 2.9-3.4, so the second wave pays where two of
+// the items in turn would outlast the longest one (2048 x 16 KiB 3.4 us per
+// block of the chain with two waves, 5.3 with one; the serving burst, whose
+// lengths spread over decades, 2.55 ms against 2.17-2.50), and costs where the
+// next messages, at 7 us per block in the pair form, wait for it: a mixed
+// kernel holds two waves per SIMD, and with both at split items 10^5 messages
+// of up to 16 KiB took 1.70 ms, with one 1.31 (4097 x 16 KiB 1.39, 1.09).
 constexpr uint32_t kSplitItemsPerSimd = 2;
 
 // The plan, made by one workgroup of the second pass once the first pass
@@ -942,7 +956,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   uint32_t* const meta = a.meta;
   uint32_t* const ctl = meta + M_CTL;
   uint32_t* const sync = meta + M_SYNC;
-  __shared__ uint32_t s_split, s_ndef, s_maxkey, s_midkey;
+  __shared__ uint32_t s_split, s_ndef, s_maxkey, s_midkey, s_nextkey;
   __shared__ unsigned long long s_useful;
   const uint32_t t = threadIdx.x;
   // The deferred sub-lists' lengths (read into a scalar register: the branch
@@ -963,7 +977,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   dirty = __builtin_amdgcn_readfirstlane(dirty);
   if (t == 0) {
     s_useful = 0ull;
-    s_maxkey = s_midkey = 0u;
+    s_maxkey = s_midkey = s_nextkey = 0u;
   }
   __syncthreads();  // every thread has read the counters
   if (t < kCopies) meta[M_DEFCNT + t * kLine] = 0u;
@@ -1029,9 +1043,9 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     ctl[CTL_USEFUL + 1] = static_cast<uint32_t>(useful >> 32);
   }
   // bucket starts; the split range ends where the keys drop below kmin
-  const uint64_t per_lane = 2u * useful / (a.lanes ? a.lanes : 1u);
+  const uint64_t bound = kSplitHalves * useful / (2u * 64u * a.simds);
   uint64_t kmin64 = kSplitMinKey;
-  if (per_lane > kmin64) kmin64 = per_lane;
+  if (bound > kmin64) kmin64 = bound;
   const uint32_t kmin = kmin64 < kKeyBins - 1u ? static_cast<uint32_t>(kmin64) : kKeyBins - 1u;
   if (t == 0) s_split = ndef;  // until a bucket that stays one lane per message
 #pragma unroll
@@ -1052,22 +1066,26 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t ct = (a.class_threads >> (4u * class_of_key(key))) & 0xFu;
     const bool split_here = ct == 2u || (ct == 0u && key >= kmin);
     if (cnt[q] && !split_here) atomicMin(&s_split, st[q]);
-    const uint32_t mid = a.split_cap / kSplitItemsPerSimd;  // the first item past one per SIMD
+    const uint32_t mid = a.simds;  // the first item past one per SIMD
     if (st[q] <= mid && mid < st[q] + cnt[q]) s_midkey = key;
   }
   __syncthreads();
   const uint32_t split_all = __builtin_amdgcn_readfirstlane(s_split);
   // When every deferred message is a split candidate and there are at most
   // twice the cap, the front waves take them all in two rounds: the excess
-  // would otherwise run one lane per message, a chain at about a third of
-  // the wide form's speed.
+  // would otherwise run in the pair form, a chain at about a third of the wide
+  // form's speed.
   const uint32_t cap =
       split_all == ndef && ndef <= 2u * a.split_cap ? 2u * a.split_cap : a.split_cap;
   const uint32_t split = split_all < cap ? split_all : cap;
+#pragma unroll
+  for (uint32_t q = 0; q < kRanksPerThread; ++q)  // (read after the scan below, whose barriers order it)
+    if (st[q] <= split && split < st[q] + cnt[q]) s_nextkey = kKeyBins - 1u - (kRanksPerThread * t + q);
   // which buckets past it take the pair form (see kPairDeepEighths)
-  uint64_t pair64 = kKeyBins;
-  if (ndef >= 2u * a.lanes) pair64 = kPairDeepEighths * useful / (8u * (a.lanes ? a.lanes : 1u)) + 1u;
-  if (ndef - split <= a.pair_cap) pair64 = 1u;
+  const uint64_t waves = a.lanes / 64u - (split ? a.simds : 0u);  // with no split items to take
+  const uint64_t slots = 2u * 64u * a.simds;                      // lanes of two waves per SIMD
+  uint64_t pair64 = kPairDeepEighths * useful / (8u * (ndef < slots ? ndef : slots)) + 1u;
+  if (ndef - split <= a.pair_cap && ndef - split <= kPairStates * waves) pair64 = 1u;
   const uint32_t pair_key = pair64 < kKeyBins ? static_cast<uint32_t>(pair64) : kKeyBins;
   // queue items over the positions past the split range
   uint32_t items[kRanksPerThread], it_sum = 0;
@@ -1096,8 +1114,15 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t item_tiles = (it_run + kBlock - 1) / kBlock;
     ctl[CTL_NITEMS] = it_run;
     ctl[CTL_SPLIT_N] = split;
-    ctl[CTL_SPLIT_WAVES] =
-        split > a.split_cap / kSplitItemsPerSimd && 5u * s_midkey > 3u * s_maxkey ? 2u : 1u;
+    const bool two = split > a.simds && 5u * s_midkey > 3u * s_maxkey &&
+                     4u * s_nextkey <= s_maxkey;
+    const uint32_t split_waves = two ? 2u : 1u;
+    ctl[CTL_SPLIT_WAVES] = split_waves;
+    // a wave that takes no split items starts on the long items at once (if
+    // there is such a wave).  2^18 mixed messages of up to 16 KiB, log-uniform:
+    // 1.95 ms when the wave of the split items took the long ones after them,
+    // 1.54 so; 2 x 10^5 of them 1.77, 1.49.
+    ctl[CTL_FRONT] = split && a.lanes > 64u * a.simds * split_waves ? split_waves : 0u;
     ctl[CTL_PAIR_KEY] = pair_key;
     ctl[CTL_ITEM_TILES] = item_tiles;
     ctl[CTL_TILES] = item_tiles + (ndef_chunks + kScatterChunks - 1) / kScatterChunks;
@@ -1302,12 +1327,13 @@ __device__ __forceinline__ void scatter_tile(const PassArgs& a, uint32_t tile, u
 // launch's workgroups, the others spinning on a published word and then
 // fencing: on the uneven 2^20 batch the plan and tiles took 84 us of it,
 // the acquire fences of hundreds of workgroups each invalidating an L2.)
-// On each SIMD one wave (the first to count itself on the SIMD's word) takes
-// items from the front, so the long absorb chains that bound the makespan run
-// from the start; the other resident waves take the shortest items from the
-// back.  (Every form raises and drops its priority by itself, so a front wave
-// has none of its own; being the oldest on its SIMD it still runs at 11.1 us
-// per block against 13.5 for the second wave.)  Both
+// On each SIMD one wave (the first to count itself on the SIMD's word, or the
+// first of those with no split items to take) takes items from the front, so
+// the long absorb chains that bound the makespan run from the start; the other
+// resident waves take the shortest items from the back.  (Every form raises and
+// drops its priority by itself, so a front wave has none of its own; being the
+// oldest on its SIMD it still runs at 11.1 us per block against 13.5 for the
+// second wave.)  Both
 // ends of a sub-queue advance one packed 64-bit counter, so no item is taken
 // twice.  A wave drains the sub-queue of its own XCD first and then the
 // others in turn, so every item is taken whatever the mapping of waves to
@@ -1356,21 +1382,21 @@ __global__ __launch_bounds__(kBlock) void k_second(PassArgs a) {
     uint32_t rank = 0;  // of this wave among those that arrived on its SIMD
     if (lane == 0) rank = atomicAdd(&a.meta[M_SIMD + simd_slot()], 1u);
     rank = __builtin_amdgcn_readfirstlane(rank);
-    const bool front = rank == 0u;
+    const bool front = rank == ctl[CTL_FRONT];
     const unsigned long long step = 1ull << (front ? 0 : 32);
     const uint32_t home = __builtin_amdgcn_s_getreg((3 << 11) | 20) & (kQueues - 1u);
-    // Split items first: the front waves hash the longest messages (bucketed
-    // positions [0, split_n)) one at a time in the wide lane-split form (half a
+    // Split items first: the first wave of each SIMD (or two) hashes the longest messages
+    // (bucketed positions [0, split_n)) one at a time in the wide lane-split form (half a
     // state word per lane), whose chain of permutations runs about four times
     // as fast as one thread's.  The XOFs squeeze in the same form.
     const uint32_t split_n = ctl[CTL_SPLIT_N];
     // With no split tail and no more queue items than SIMDs, the front waves
     // (one per SIMD) take every item: a second wave on a SIMD would share its
     // issue slots and stretch both items' chains while other SIMDs idle.
-    if (!front && split_n == 0u && n_items <= a.split_cap / kSplitItemsPerSimd) return;
+    if (!front && split_n == 0u && n_items <= a.simds) return;
     {
       if (split_n && rank < ctl[CTL_SPLIT_WAVES]) {
-        if (rank) __builtin_amdgcn_s_sleep(127);  // the front waves of all SIMDs first
+        if (rank) __builtin_amdgcn_s_sleep(127);  // the first waves of all SIMDs first
         namespace wd = kb::wide;
         wd::WideLane L;
         wd::setup(L, lane);
@@ -1871,9 +1897,10 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   a.order = w.order;
   a.items = w.items;
   a.steps = tile && tile->steps_per_item > 0 ? static_cast<uint32_t>(tile->steps_per_item) : 4u;
-  // at most kSplitItemsPerSimd wide split items (one message) for each SIMD's front wave (the per-bucket form takes none)
-  a.split_cap = !per_bucket ? kSplitItemsPerSimd * 4u * static_cast<uint32_t>(cus) : 0u;
-  a.pair_cap = !per_bucket ? 2u * kPairStates * 4u * static_cast<uint32_t>(cus) : 0u;
+  // at most kSplitItemsPerSimd wide split items (one message) per SIMD (the per-bucket form takes none)
+  a.simds = 4u * static_cast<uint32_t>(cus);
+  a.split_cap = !per_bucket ? kSplitItemsPerSimd * a.simds : 0u;
+  a.pair_cap = !per_bucket ? 2u * kPairStates * a.simds : 0u;
   a.class_steps = 0;
   a.class_threads = 0;
   for (int c = 0; tile && c < KB_NB_CLASSES; ++c) {  // ranges checked by check_tile
