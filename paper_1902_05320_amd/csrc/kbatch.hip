@@ -72,6 +72,7 @@ enum : int {
   CTL_SPLIT_N = 6,      // bucketed order positions [0, CTL_SPLIT_N) are hashed in the wide split form
   CTL_PAIR_KEY = 7,     // items of at least this many blocks are hashed in the pair form
   CTL_FRONT = 10,       // the wave of a SIMD (in order of arrival) that takes items from the front
+  CTL_STEPS = 11,       // permutations per lane in an item, where neither the tile nor its class says
   CTL_USEFUL = 8,       // uint64 (words 8, 9): block counts of the deferred messages
   CTL_DPREFIX = 16,     // words 16..24: exclusive prefix of the deferred sub-list lengths
   CTL_WORDS = 64
@@ -144,7 +145,7 @@ struct PassArgs {
   uint32_t* deferred;   // deferred chunk indices: kCopies sub-lists of defer_seg entries
   uint32_t* order;      // bucketed order of the deferred messages, n entries
   WorkItem* items;      // queue items, max_items(n) entries
-  uint32_t steps;       // permutations per lane in one queue item
+  uint32_t steps;       // permutations per lane in one queue item (0 = the plan's choice)
   uint32_t simds;       // SIMDs of the chip
   uint32_t pair_cap;    // past the split tail, at most this many messages go to the pair form all
   uint32_t split_cap;   // most messages the split tail may take (SHA-3 variants)
@@ -883,10 +884,11 @@ __device__ __forceinline__ uint32_t class_of_key(uint32_t key) {
   return c < KB_NB_CLASSES - 1u ? c : KB_NB_CLASSES - 1u;
 }
 
-// Steps per queue item for a bucket: its class's tuned value, else the default.
-__device__ __forceinline__ uint32_t steps_of(const PassArgs& a, uint32_t key) {
+// Steps per queue item for a bucket: its class's tuned value, else the tile's,
+// else the plan's.
+__device__ __forceinline__ uint32_t steps_of(const PassArgs& a, uint32_t key, uint32_t plan_steps) {
   const uint32_t s = static_cast<uint32_t>(a.class_steps >> (8u * class_of_key(key))) & 0xFFu;
-  return s ? s : a.steps;
+  return s ? s : a.steps ? a.steps : plan_steps;
 }
 
 // Whether a bucket's messages past the split range take the pair form (a
@@ -930,10 +932,20 @@ constexpr uint64_t kSplitHalves = 5;
 //     2.45-2.49 ms, from 9/8 2.29, 11/8 2.13, 12/8 2.12, 13/8 2.31.  (A SIMD
 //     left to the one long item instead gained nothing: 2.36.)  10^5 mixed
 //     messages of up to 16 KiB, log-uniform: no pairs 1.31 ms, 12/8 1.16.
+// A batch that the first bound lets go to pairs whole has a wave for every 32
+// (or 64) messages: an item is then one message per lane, not kSteps
+// permutations' worth of them one after the other.  10000 SHA3-224 messages of
+// up to 200 bytes (one block or two) 97 us with four, 66 with one; SHA3-256 93
+// and 65.  And where that makes more than one pair wave per SIMD, messages of
+// fewer than kPairShortKey blocks stay at one thread each: 50000 SHA3-512
+// messages of 3 blocks 85 us in pairs and 79 so, of 4 blocks 89 and 88, of 6
+// 101 and 105, of 12 145 and 157.
 // A batch of equal messages above the first bound has none of these: one
 // thread per message keeps the waves of a SIMD at two (100003 x 1001 B
 // SHA3-384 291 us, 320 with pairs).
 constexpr uint64_t kPairDeepEighths = 12;
+constexpr uint32_t kPairShortKey = 5;
+constexpr uint32_t kSteps = 4;
 // Wide split items (messages) per SIMD.  A SIMD's front wave takes them one
 // after the other, unless the middle one is longer than 3/5 of the longest and
 // no message past the split range is longer than a quarter of it: then a second
@@ -1085,7 +1097,9 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   const uint64_t waves = a.lanes / 64u - (split ? a.simds : 0u);  // with no split items to take
   const uint64_t slots = 2u * 64u * a.simds;                      // lanes of two waves per SIMD
   uint64_t pair64 = kPairDeepEighths * useful / (8u * (ndef < slots ? ndef : slots)) + 1u;
-  if (ndef - split <= a.pair_cap && ndef - split <= kPairStates * waves) pair64 = 1u;
+  const bool whole = ndef - split <= a.pair_cap && ndef - split <= kPairStates * waves;
+  if (whole) pair64 = ndef - split <= kPairStates * static_cast<uint64_t>(a.simds) ? 1u : kPairShortKey;
+  const uint32_t steps = whole ? 1u : kSteps;
   const uint32_t pair_key = pair64 < kKeyBins ? static_cast<uint32_t>(pair64) : kKeyBins;
   // queue items over the positions past the split range
   uint32_t items[kRanksPerThread], it_sum = 0;
@@ -1093,7 +1107,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   for (uint32_t q = 0; q < kRanksPerThread; ++q) {
     const uint32_t key = kKeyBins - 1u - (kRanksPerThread * t + q);
     const uint32_t b = st[q] > split ? st[q] : split, e = st[q] + cnt[q];
-    const uint32_t per = item_msgs(key, steps_of(a, key), pair_bucket(a, key, pair_key));
+    const uint32_t per = item_msgs(key, steps_of(a, key, steps), pair_bucket(a, key, pair_key));
     items[q] = e > b ? (e - b + per - 1u) / per : 0u;
     it_sum += items[q];
   }
@@ -1124,6 +1138,7 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     // 1.54 so; 2 x 10^5 of them 1.77, 1.49.
     ctl[CTL_FRONT] = split && a.lanes > 64u * a.simds * split_waves ? split_waves : 0u;
     ctl[CTL_PAIR_KEY] = pair_key;
+    ctl[CTL_STEPS] = steps;
     ctl[CTL_ITEM_TILES] = item_tiles;
     ctl[CTL_TILES] = item_tiles + (ndef_chunks + kScatterChunks - 1) / kScatterChunks;
   }
@@ -1263,7 +1278,7 @@ __device__ __forceinline__ void items_tile(const PassArgs& a, uint32_t tile) {
   }
   const uint32_t key = kKeyBins - 1u - lo;
   const bool pair = pair_bucket(a, key, ctl[CTL_PAIR_KEY]);
-  const uint32_t per = item_msgs(key, steps_of(a, key), pair);
+  const uint32_t per = item_msgs(key, steps_of(a, key, ctl[CTL_STEPS]), pair);
   const uint32_t first_item = lo ? iend[lo - 1] : 0u;
   const uint32_t split = ctl[CTL_SPLIT_N];  // positions before it are split work
   const uint32_t start = meta[M_START + key];
@@ -1896,7 +1911,7 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   a.defer_seg = static_cast<uint32_t>(defer_seg_of(b.n));
   a.order = w.order;
   a.items = w.items;
-  a.steps = tile && tile->steps_per_item > 0 ? static_cast<uint32_t>(tile->steps_per_item) : 4u;
+  a.steps = tile && tile->steps_per_item > 0 ? static_cast<uint32_t>(tile->steps_per_item) : 0u;
   // at most kSplitItemsPerSimd wide split items (one message) per SIMD (the per-bucket form takes none)
   a.simds = 4u * static_cast<uint32_t>(cus);
   a.split_cap = !per_bucket ? kSplitItemsPerSimd * a.simds : 0u;

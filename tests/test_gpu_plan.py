@@ -76,6 +76,49 @@ def test_long_messages_past_the_split_tail(kb, o2, case):
     _check(kb, o2, b)
 
 
+@pytest.mark.parametrize("n", [5_000, 32_768, 32_769, 65_536, 65_537])
+@pytest.mark.parametrize("steps", [0, 1, 7])
+def test_short_messages_in_items_of_their_own(kb, o2, n, steps):
+    # one to six blocks: pairs of one message each up to 32768, from five blocks
+    # on up to 65536, then several messages to an item; a tile's steps hold
+    # whatever the batch
+    rng = np.random.Generator(np.random.PCG64(134))
+    lens = rng.choice([40, 71, 72, 143, 144, 150, 287, 288, 360, 431], n)
+    lens[::64] = 600  # no chunk of one-block messages
+    b = wl.explicit(lens, seed=135, variant=rng.integers(0, 4, n).astype(np.uint8), gap=1, lead=3)
+    t = None
+    if steps:
+        t = kb.Tile()
+        t.steps_per_item = steps
+    _say("short messages", n, "steps", steps)
+    _check(kb, o2, b, variants=(-1, 0, 3), tile=t)
+
+
+def test_short_uneven_batch_keeps_its_time(kb):
+    # 10^4 SHA3-224 messages of one block or two, against the same with the four
+    # steps per item of a tile: 0.68 of the time, 1.0 when the plan took four too
+    import torch
+    rng = np.random.Generator(np.random.PCG64(6))
+    n = 10_000
+    lens = wl.log_uniform_lengths(rng, n, 200)
+    offs = np.cumsum(lens) - lens
+    data = torch.randint(0, 256, (int(lens.sum()),), dtype=torch.uint8, device="cuda")
+    o, l = torch.from_numpy(offs).cuda(), torch.from_numpy(lens).cuda()
+    out = torch.empty((n, 28), dtype=torch.uint8, device="cuda")
+    four = kb.Tile()
+    four.steps_per_item = 4
+    best = {}
+    for tile in (None, four) * 10:
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(10):
+            kb.keccak_batch(0, data, o, l, out=out, tile=tile, check_bounds=False)
+        torch.cuda.synchronize()
+        best[tile is None] = min(best.get(tile is None, 1e9), time.perf_counter() - t)
+    _say("short uneven 10000", {k: round(1e5 * v) for k, v in best.items()})
+    assert best[True] < 0.85 * best[False]
+
+
 @pytest.mark.parametrize("waves", [1, 2])
 def test_split_tail_with_few_waves(kb, o2, waves):
     # with one wave per SIMD none is left beside the split tail
