@@ -112,17 +112,20 @@ __device__ __forceinline__ void load_halves(HalfDw<V>& d, const uint8_t* msg, ui
 #pragma unroll
     for (int q = 0; q < HalfDw<V>::kQ; ++q) {
       const int at = 32 * q + 16 * static_cast<int>(h);
+      // (a value of its own, stored to d once: with the elements stored in the
+      // branches the compiler kept d in private memory in the mixed form)
+      Words4 v = {0u, 0u, 0u, 0u};
       if (32 * q + 32 <= kAll || at + 16 <= R) {
-        const Words4 v = *reinterpret_cast<const Words4*>(p + 32 * q);
-        d.w[4 * q] = v.x;
-        d.w[4 * q + 1] = v.y;
-        d.w[4 * q + 2] = v.z;
-        d.w[4 * q + 3] = v.w;
+        v = *reinterpret_cast<const Words4*>(p + 32 * q);
       } else if (at + 8 == R) {
-        const Words2 v = *reinterpret_cast<const Words2*>(p + 32 * q);
-        d.w[4 * q] = v.x;
-        d.w[4 * q + 1] = v.y;
+        const Words2 half = *reinterpret_cast<const Words2*>(p + 32 * q);
+        v.x = half.x;
+        v.y = half.y;
       }
+      d.w[4 * q] = v.x;
+      d.w[4 * q + 1] = v.y;
+      d.w[4 * q + 2] = v.z;
+      d.w[4 * q + 3] = v.w;
     }
     return;
   }

@@ -1,8 +1,10 @@
-"""The GPU code in the built library, from its ELF headers alone (no GPU
-needed): the constant tables are reached directly, not through an address
-table."""
+"""The GPU code in the built library, from its ELF headers and kernel metadata
+alone (no GPU needed): no kernel keeps registers or arrays in private memory,
+and the constant tables are reached directly, not through an address table."""
 
 import struct
+
+import pytest
 
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
@@ -31,6 +33,32 @@ def _sections(elf):
     raw = [struct.unpack_from("<IIQQQQ", elf, shoff + 64 * k) for k in range(num)]
     base = raw[names][4]
     return [(elf[base + r[0]:elf.index(b"\0", base + r[0])].decode(), r[1], r[4], r[5]) for r in raw]
+
+
+def _kernels():
+    msgpack = pytest.importorskip("msgpack")
+    out = {}
+    for elf in _code_objects():
+        for name, kind, off, size in _sections(elf):
+            if kind != 7:  # SHT_NOTE
+                continue
+            nsz, dsz, ntype = struct.unpack_from("<III", elf, off)
+            if ntype != 32:  # NT_AMDGPU_METADATA
+                continue
+            desc = off + 12 + (nsz + 3) // 4 * 4
+            for k in msgpack.unpackb(elf[desc:desc + dsz])["amdhsa.kernels"]:
+                out[k[".name"]] = k
+    return out
+
+
+def test_no_kernel_uses_private_memory():
+    # (private memory is allocated by the runtime at a kernel's first launch,
+    # and an array in it is a round trip to memory in the middle of a chain)
+    kernels = _kernels()
+    assert len(kernels) > 60
+    bad = {n: k[".private_segment_fixed_size"] for n, k in kernels.items()
+           if k[".private_segment_fixed_size"] or k.get(".vgpr_spill_count")}
+    assert not bad, bad
 
 
 def test_constant_tables_are_reached_directly():
