@@ -147,6 +147,7 @@ struct PassArgs {
   WorkItem* items;      // queue items, max_items(n) entries
   uint32_t steps;       // permutations per lane in one queue item (0 = the plan's choice)
   uint32_t simds;       // SIMDs of the chip
+  uint32_t squeezes;    // permutations between the output blocks of a message (XOFs)
   uint32_t pair_cap;    // past the split tail, at most this many messages go to the pair form all
   uint32_t split_cap;   // most messages the split tail may take (SHA-3 variants)
   // Per block-count class c, packed so that no array is indexed at run time
@@ -1055,9 +1056,11 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     ctl[CTL_USEFUL + 1] = static_cast<uint32_t>(useful >> 32);
   }
   // bucket starts; the split range ends where the keys drop below kmin
-  const uint64_t bound = kSplitHalves * useful / (2u * 64u * a.simds);
+  // (a message's chain is its blocks and, for the XOFs, `squeezes` more)
+  const uint64_t perms = useful + static_cast<uint64_t>(a.squeezes) * ndef;
+  const uint64_t bound = kSplitHalves * perms / (2u * 64u * a.simds);
   uint64_t kmin64 = kSplitMinKey;
-  if (bound > kmin64) kmin64 = bound;
+  if (bound > kmin64 + a.squeezes) kmin64 = bound - a.squeezes;
   const uint32_t kmin = kmin64 < kKeyBins - 1u ? static_cast<uint32_t>(kmin64) : kKeyBins - 1u;
   if (t == 0) s_split = ndef;  // until a bucket that stays one lane per message
 #pragma unroll
@@ -1096,9 +1099,13 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
   // which buckets past it take the pair form (see kPairDeepEighths)
   const uint64_t waves = a.lanes / 64u - (split ? a.simds : 0u);  // with no split items to take
   const uint64_t slots = 2u * 64u * a.simds;                      // lanes of two waves per SIMD
-  uint64_t pair64 = kPairDeepEighths * useful / (8u * (ndef < slots ? ndef : slots)) + 1u;
+  uint64_t pair64 = kPairDeepEighths * perms / (8u * (ndef < slots ? ndef : slots)) + 1u;
+  pair64 = pair64 > a.squeezes + 1u ? pair64 - a.squeezes : 1u;
   const bool whole = ndef - split <= a.pair_cap && ndef - split <= kPairStates * waves;
-  if (whole) pair64 = ndef - split <= kPairStates * static_cast<uint64_t>(a.simds) ? 1u : kPairShortKey;
+  if (whole) {
+    const bool one_wave = ndef - split <= kPairStates * static_cast<uint64_t>(a.simds);
+    pair64 = one_wave || a.squeezes + 1u >= kPairShortKey ? 1u : kPairShortKey - a.squeezes;
+  }
   const uint32_t steps = whole ? 1u : kSteps;
   const uint32_t pair_key = pair64 < kKeyBins ? static_cast<uint32_t>(pair64) : kKeyBins;
   // queue items over the positions past the split range
@@ -1128,8 +1135,9 @@ __device__ void make_plan(const PassArgs& a, uint32_t* scratch) {
     const uint32_t item_tiles = (it_run + kBlock - 1) / kBlock;
     ctl[CTL_NITEMS] = it_run;
     ctl[CTL_SPLIT_N] = split;
-    const bool two = split > a.simds && 5u * s_midkey > 3u * s_maxkey &&
-                     4u * s_nextkey <= s_maxkey;
+    const uint32_t more = a.squeezes;
+    const bool two = split > a.simds && 5u * (s_midkey + more) > 3u * (s_maxkey + more) &&
+                     (split == ndef || 4u * (s_nextkey + more) <= s_maxkey + more);
     const uint32_t split_waves = two ? 2u : 1u;
     ctl[CTL_SPLIT_WAVES] = split_waves;
     // a wave that takes no split items starts on the long items at once (if
@@ -1916,6 +1924,10 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   a.steps = tile && tile->steps_per_item > 0 ? static_cast<uint32_t>(tile->steps_per_item) : 0u;
   // at most kSplitItemsPerSimd wide split items (one message) per SIMD (the per-bucket form takes none)
   a.simds = 4u * static_cast<uint32_t>(cus);
+  if constexpr (V >= kShake128) {
+    const uint64_t more = (b.stride - 1) / SpongeShape<V>::kMaxRate;
+    a.squeezes = more < 0xFFFFu ? static_cast<uint32_t>(more) : 0xFFFFu;
+  }
   a.split_cap = !per_bucket ? kSplitItemsPerSimd * a.simds : 0u;
   a.pair_cap = !per_bucket ? 2u * kPairStates * a.simds : 0u;
   a.class_steps = 0;

@@ -76,6 +76,24 @@ def test_long_messages_past_the_split_tail(kb, o2, case):
     _check(kb, o2, b)
 
 
+@pytest.mark.parametrize("security", [128, 256])
+@pytest.mark.parametrize("n,out_len", [(5_000, 700), (40_000, 100), (40_000, 700), (70_001, 700)])
+def test_xof_plan_counts_the_squeezes(kb, o2, security, n, out_len):
+    # chains of one to ten blocks and none or several more permutations for the
+    # output: pairs whole, by the shortest chain, by the mean chain
+    import torch
+    rng = np.random.Generator(np.random.PCG64(136))
+    b = wl.explicit(wl.log_uniform_lengths(rng, n, 1300), seed=137, gap=1, lead=3)
+    data, offs, lens, _ = _dev(b)
+    _say("xof plan", security, n, out_len)
+    got = kb.keccak_batch_xof(security, data, offs, lens, out_len)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    for i in range(0, n, 7):
+        m = b.data[b.offsets[i]:b.offsets[i] + b.lengths[i]].tobytes()
+        assert got[i].tobytes() == o2.shake(security, m, out_len), i
+
+
 @pytest.mark.parametrize("n", [5_000, 32_768, 32_769, 65_536, 65_537])
 @pytest.mark.parametrize("steps", [0, 1, 7])
 def test_short_messages_in_items_of_their_own(kb, o2, n, steps):
