@@ -78,7 +78,8 @@ enum kb_mode {
 };
 
 /*
- * Tuning knobs of the persistent form; a zero field means "library default".
+ * Tuning knobs of the persistent form; a zero field means "library default",
+ * and a tile of zeros is the same as none.
  * Messages are grouped by block count nb = floor(L / R) + 1 into
  * KB_NB_CLASSES classes, class c = floor(log2(nb)) capped at
  * KB_NB_CLASSES - 1 (1, 2-3, 4-7, ..., 128 or more blocks); the class
@@ -95,7 +96,8 @@ enum kb_staging {
 typedef struct kb_tile {
   int32_t block_threads;    /* 0 or 256: the hashing kernels use 256-thread workgroups */
   int32_t waves_per_simd;   /* persistent grid: resident waves per SIMD (1..8) */
-  int32_t steps_per_item;   /* wave-blocks of work per queue item (>= 1) */
+  int32_t steps_per_item;   /* wave-blocks of work per queue item (1..255; default 4, or one
+                               message per lane where the grid has a wave for every message) */
   int32_t staging;          /* kb_staging: how a message's next block reaches the sponge */
   int32_t class_steps[KB_NB_CLASSES];    /* per class: steps per queue item (0 = steps_per_item) */
   int32_t class_threads[KB_NB_CLASSES];  /* per class: threads per state, 1 (one lane hashes a
@@ -205,7 +207,8 @@ int merkle_root(int variant, const uint8_t* d_data, uint64_t total_len, uint64_t
  * steps_per_item {1, 2, 4, 8, 16, 32}; then threads per state by
  * block-count class (the wide split tail from each class present upward, or
  * one lane everywhere); then steps per queue item for each class present
- * {1, 4, 16}.  Every candidate's digests are first compared with the plain
+ * {1, 4, 16}; then no tile at all (a zero *best if that is the fastest: the
+ * library's own choice, which for a small batch is one wide launch).  Every candidate's digests are first compared with the plain
  * form's bit for bit (a candidate that differs is discarded and counted in
  * *rejected); the verified ones are timed with HIP events (median of `reps`
  * runs).  The fastest goes to *best and its time to *best_ms.  Arguments as
@@ -231,7 +234,9 @@ int keccak_autotune(int variant, const uint8_t* d_variants, const uint8_t* d_dat
  * `variant` (-1 = mixed), into the cache file at `path` (created if
  * missing), replacing entries with the same key; `ms` is recorded beside it
  * (< 0: none).  Entries are written for the launch-wide knobs and for each
- * class whose class_steps or class_threads is set.  KB_EINVAL for a NULL
+ * class whose class_steps or class_threads is set; a tile that sets nothing
+ * (the library's own choice) also removes the class entries of that batch
+ * class, so that a batch call then runs as with no tile.  KB_EINVAL for a NULL
  * path or tile, an unknown variant, n == 0, only one of arch/rocm given, a
  * malformed existing file or a write failure.
  *

@@ -15,6 +15,8 @@ hipGraph_t native_graph(kb_graph* g);
 // `path` (NULL: $KBATCH_TUNE) holds for a batch of n messages of `variant`
 // (-1 = mixed) on the current device; 1 if found, 0 if not, < 0 on error.
 int tune_lookup(const char* path, int variant, uint64_t n, kb_tile* out);
+// Whether a tile sets nothing that a launch depends on.
+bool is_default_tile(const kb_tile& t);
 // Record the tile the calling thread's batch call runs (keccak_last_tile).
 void note_tile(const kb_tile* t, int cached);
 // Block-count class floor(log2(blocks)) capped at KB_NB_CLASSES - 1, and

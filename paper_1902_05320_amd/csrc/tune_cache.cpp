@@ -18,11 +18,14 @@
 // device applies per bucket of equal block counts (steps per queue item and
 // threads per state) carry the block-count class of the bucket, so a launch
 // over a batch that spans several classes takes each class's own choice.
+// An entry of zeros under "*" with no class entries beside it is the library's
+// own choice (a batch call then runs as if no file were named).
 //
 // batch_class = floor(log2(n)); nb_class = floor(log2(blocks)), capped at
 // KB_NB_CLASSES - 1 (blocks = floor(L / R) + 1 of a message).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cctype>
 #include <cstdio>
 #include <cstdlib>
@@ -413,6 +416,12 @@ int nb_class_of(uint64_t blocks) {
 
 int batch_class_of(uint64_t n) { return floor_log2(n ? n : 1); }
 
+bool is_default_tile(const kb_tile& t) {
+  bool any = t.waves_per_simd || t.steps_per_item || t.staging;
+  for (int c = 0; c < KB_NB_CLASSES; ++c) any = any || t.class_steps[c] || t.class_threads[c];
+  return !any;
+}
+
 // The tile for a batch from the file `path` (or KBATCH_TUNE when NULL).
 // Returns 1 if any entry matched, 0 if none (or no file is named), <0 on a
 // malformed file.
@@ -494,6 +503,14 @@ int keccak_tune_store(const char* path, const char* arch_in, const char* rocm_in
     e.threads_per_state = tile->class_threads[c];
     add.push_back(e);
   }
+  // a tile that chooses nothing takes the place of every choice made before
+  if (kb::is_default_tile(*tile))
+    es.erase(std::remove_if(es.begin(), es.end(),
+                            [&](const Entry& e) {
+                              return e.nb_class >= 0 && e.arch == arch && e.rocm == rocm &&
+                                     e.variant == vname && e.batch_class == base.batch_class;
+                            }),
+             es.end());
   for (const Entry& a : add) {
     bool replaced = false;
     for (Entry& e : es)
