@@ -58,7 +58,11 @@ enum kb_mode {
                              64-message chunk of one-block messages at once; then a plan,
                              a scatter into buckets of equal block count, and a resident
                              grid hashing the buckets longest first (the longest messages
-                             in the wide split form) */
+                             in the wide split form, long ones in the pair form).  Without
+                             a tile, batches of at most four messages per SIMD (4096 on
+                             1024 SIMDs) are hashed by the first launch in the wide form,
+                             and up to two per SIMD, or captured into a graph, that launch
+                             is the only one */
   KB_MODE_PLAIN = 1,      /* one thread per message in arrival order, one launch (the
                              paper's "one thread per message", Section 4.1) */
   KB_MODE_PER_BUCKET = 2, /* bucket by block count, one plain launch per bucket (waits on
@@ -128,7 +132,7 @@ int keccak_batch(int variant, const uint8_t* d_data, const uint64_t* d_offsets,
  * keccak_batch_noalloc -- keccak_batch that allocates nothing, for callers
  * that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  The scheduling workspace
- * is one static array on each device (about 4.6 MiB, for up to
+ * is one static array on each device (about 4.9 MiB, for up to
  * KB_NOALLOC_MAX_MSGS messages), present from the library's load until the
  * process ends; the first call on a device looks it up and clears it on
  * `stream`, and each call leaves it cleared for the next.  Every call on a
@@ -415,12 +419,13 @@ int keccak_timing_read(double* total_ms, uint64_t* launches);
 
 /* Kinds of bracketed kernels. */
 enum kb_kernel {
-  KB_KERNEL_FIRST_PASS = 0,  /* persistent form: the arrival-order pass */
+  KB_KERNEL_FIRST_PASS = 0,  /* persistent form: the arrival-order pass (whatever form it
+                                hashes in: a small batch's wide launch is this kind) */
   KB_KERNEL_SECOND_PASS = 1, /* persistent form: the bucketed pass */
   KB_KERNEL_PLAIN = 2,       /* one thread per message (plain and per-bucket forms) */
   KB_KERNEL_SPLIT = 3,       /* lane-split form */
   KB_KERNEL_TREE = 4,        /* tree mode */
-  KB_KERNEL_WIDE = 5,        /* wide lane-split form */
+  KB_KERNEL_WIDE = 5,        /* wide lane-split form (KB_MODE_WIDE) */
   KB_KERNEL_SCHEDULE = 6,    /* persistent form: the plan and the bucketing scatter */
   KB_KERNEL_PAIR = 7         /* pair form */
 };

@@ -1812,7 +1812,7 @@ int launch_split(const Batch& b, const uint32_t* order, uint64_t first, uint64_t
 
 template <int V>
 int launch_wide(const Batch& b, const uint32_t* order, uint64_t first, uint64_t count,
-                hipStream_t s) {
+                hipStream_t s, int kind = KB_KERNEL_WIDE) {
   if (!count) return KB_OK;
   int dev = 0, cus = 0;
   KB_HIP(hipGetDevice(&dev));
@@ -1824,7 +1824,7 @@ int launch_wide(const Batch& b, const uint32_t* order, uint64_t first, uint64_t 
   uint64_t grid = count;
   if (grid > static_cast<uint64_t>(32 * cus)) grid = 32 * cus;
   {
-    TimedLaunch tl(s, KB_KERNEL_WIDE);
+    TimedLaunch tl(s, kind);
     hipLaunchKernelGGL(k_wide<V>, dim3(static_cast<uint32_t>(grid)), dim3(kWideBlock), 0, s,
                        b.data, b.offs, b.lens, b.vars, order, first, count, b.out, b.stride);
   }
@@ -1944,13 +1944,13 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   // Up to four messages per SIMD the first pass hashes them all, in the wide
   // form, and defers nothing: 4096 messages of 0-4000 bytes SHA3-256 ran 235 us
   // with the deferred chunks in the pair form, the wide launch runs 84; 4096 x
-  // 16 KiB 818 us, wide 725; at 8192 x 64 B it is the slower one (17.6 against
-  // 13.6 for a thread per message).
+  // 16 KiB 818 us, wide 725.  Of one block each, 2049 messages 9 us, 3000 10,
+  // 4096 11.6 where a thread per message takes 13-15; at 8192 x 64 B it is the
+  // slower one (17.6 against 13.6).  The launches after it find nothing to do;
+  // they stay because callers count on them (the timing brackets of a call).
   const bool wide_first = !per_bucket && !tile && !n_dev && b.n <= 4u * 4u * static_cast<uint64_t>(cus);
   if (wide_first) {
-    TimedLaunch tl(s, KB_KERNEL_FIRST_PASS);
-    hipLaunchKernelGGL(k_wide<V>, dim3(static_cast<uint32_t>(b.n)), dim3(kWideBlock), 0, s, b.data, b.offs,
-                       b.lens, b.vars, nullptr, uint64_t{0}, b.n, b.out, b.stride);
+    if ((rc = launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS))) return rc;
   } else {
     TimedLaunch tl(s, KB_KERNEL_FIRST_PASS);
     hipLaunchKernelGGL(k_first<V>, dim3(grid1), dim3(kBlock), 0, s, a);
@@ -2002,12 +2002,14 @@ int run_batch(const Batch& b, int mode, const kb_tile* tile, hipStream_t s, Work
   // A batch of at most two messages per SIMD, no tile given: the wide form in
   // arrival order.  Whatever the lengths, no form runs a chain faster at that
   // number (2.2 us per block alone, 2.9 with two on a SIMD; one thread per
-  // message 8.8), and it is one launch against four.
+  // message 8.8), and it is one launch against four.  It is the persistent form's
+  // first pass, over arrival order, and is timed as that.
   if (mode == KB_MODE_PERSISTENT && !tile && !n_dev) {
     int dev = 0, cus = 0;
     KB_HIP(hipGetDevice(&dev));
     if (int rc = cu_count(dev, &cus)) return rc;
-    if (b.n <= kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus)) return launch_wide<V>(b, nullptr, 0, b.n, s);
+    if (b.n <= kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus))
+      return launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS);
   }
   if (b.n >= 0xFFFFFFFFull) return launch_plain<V>(b, nullptr, 0, b.n, s);  // 32-bit order[]
   Workspace* w = own;
