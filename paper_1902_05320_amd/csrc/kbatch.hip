@@ -2709,10 +2709,15 @@ int keccak_check_bounds(const uint64_t* d_offsets, const uint64_t* d_lengths, ui
   if (!bad) return fail(KB_ENOMEM, "no host memory for the bounds check");
   hipLaunchKernelGGL(k_check_bounds, dim3(static_cast<uint32_t>(blocks)), dim3(kBlock), 0, stream,
                      d_offsets, d_lengths, n, data_bytes, bad);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  // (after an error the word stays taken: the kernel may still write it)
-  if (e != hipSuccess) return fail(KB_EHIP, "bounds check: %s", hipGetErrorString(e));
+  const hipError_t launched = hipGetLastError();
+  const hipError_t waited = hipStreamSynchronize(stream);
+  if (launched != hipSuccess || waited != hipSuccess) {
+    if (waited == hipSuccess) {  // (else the word stays taken: the kernel may still write it)
+      *bad = 0u;
+      g_check.give(bad);
+    }
+    return fail(KB_EHIP, "bounds check: %s", hipGetErrorString(launched != hipSuccess ? launched : waited));
+  }
   *inside = *static_cast<volatile uint32_t*>(bad) == 0u;
   *bad = 0u;
   g_check.give(bad);
