@@ -1859,9 +1859,8 @@ int launch_pair(const Batch& b, const uint32_t* order, uint64_t first, uint64_t 
 // and asked on every call it was a large part of a small batch's host time.
 std::map<std::pair<int, const void*>, int> g_occupancy;
 
-int resident_grid(const void* kernel, const kb_tile* tile, int cus, uint32_t* grid) {
-  int dev = 0, per_cu = 0;
-  KB_HIP(hipGetDevice(&dev));
+int resident_grid(const void* kernel, const kb_tile* tile, int dev, int cus, uint32_t* grid) {
+  int per_cu = 0;
   {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_occupancy.find({dev, kernel});
@@ -1894,20 +1893,16 @@ const void* second_pass_kernel(const kb_tile* tile) {
 // bucket sizes read back on the host.
 template <int V>
 int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hipStream_t s,
-                 const uint32_t* n_dev) {
+                 const uint32_t* n_dev, int dev, int cus) {
   const bool per_bucket = mode == KB_MODE_PER_BUCKET;
-  int dev = 0, cus = 0;
-  KB_HIP(hipGetDevice(&dev));
-  int rc = cu_count(dev, &cus);
-  if (rc) return rc;
+  int rc = KB_OK;
   uint32_t grid1 = 0, grid2 = 0;
   // first pass: one 64-message chunk per wave
   const uint64_t g1 = (b.n + kBlock - 1) / kBlock;
   if (g1 > 0x7FFFFFFFull) return fail(KB_EINVAL, "batch too large for one launch");
   grid1 = static_cast<uint32_t>(g1 ? g1 : 1);
   const void* second = second_pass_kernel<V>(tile);
-  if (!rc) rc = resident_grid(second, tile, cus, &grid2);
-  if (rc) return rc;
+  if ((rc = resident_grid(second, tile, dev, cus, &grid2))) return rc;
   PassArgs a{};
   a.data = b.data;
   a.offs = b.offs;
@@ -2004,18 +1999,17 @@ int run_batch(const Batch& b, int mode, const kb_tile* tile, hipStream_t s, Work
   // number (2.2 us per block alone, 2.9 with two on a SIMD; one thread per
   // message 8.8), and it is one launch against four.  It is the persistent form's
   // first pass, over arrival order, and is timed as that.
-  if (mode == KB_MODE_PERSISTENT && !tile && !n_dev) {
-    int dev = 0, cus = 0;
-    KB_HIP(hipGetDevice(&dev));
-    if (int rc = cu_count(dev, &cus)) return rc;
-    if (b.n <= kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus))
-      return launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS);
-  }
+  int dev = 0, cus = 0;
+  KB_HIP(hipGetDevice(&dev));
+  if (int rc = cu_count(dev, &cus)) return rc;
+  if (mode == KB_MODE_PERSISTENT && !tile && !n_dev &&
+      b.n <= kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus))
+    return launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS);
   if (b.n >= 0xFFFFFFFFull) return launch_plain<V>(b, nullptr, 0, b.n, s);  // 32-bit order[]
   Workspace* w = own;
   int rc = own ? KB_OK : get_ws(s, b.n, 0, &w);
   if (rc) return rc;
-  return run_two_pass<V>(b, *w, mode, tile, s, n_dev);
+  return run_two_pass<V>(b, *w, mode, tile, s, n_dev, dev, cus);
 }
 
 // A tile that chooses nothing is no tile: the library's own dispatch, which for
