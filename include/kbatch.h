@@ -172,8 +172,8 @@ int keccak_batch_xof(int security, const uint8_t* d_data, const uint64_t* d_offs
 
 /*
  * keccak_batch_xof_ex -- keccak_batch_xof with an explicit scheduling mode
- * (KB_MODE_PERSISTENT, _PLAIN, _PER_BUCKET, _SPLIT or _WIDE; in the split
- * forms five or 50 lanes share each state and squeeze it, which shortens each
+ * (KB_MODE_PERSISTENT, _PLAIN, _PER_BUCKET, _SPLIT, _WIDE or _PAIR; in the split
+ * forms five, 50 or two lanes share each state and squeeze it, which shortens each
  * message's chain of permutations for a few long messages).  Same output;
  * KB_EINVAL for an unknown mode.
  */
@@ -197,9 +197,8 @@ int keccak_batch_ex(int variant, const uint8_t* d_variants, const uint8_t* d_dat
  * empty leaf).  Leaf digest = H(leaf); a parent = H(left || right) over the
  * two D-byte child digests; an unpaired last node at a level is carried up
  * unchanged.  H is the SHA-3 `variant`.  The D-byte root is written to
- * d_root (device memory).  leaf_size 0 is KB_EINVAL.  Leaves take a faster
- * load path when leaf_size, total_len and d_data are all multiples of 8; the
- * root does not depend on it.
+ * d_root (device memory).  leaf_size 0 is KB_EINVAL.  Any alignment of
+ * d_data and d_root and any sizes are taken.
  */
 int merkle_root(int variant, const uint8_t* d_data, uint64_t total_len, uint64_t leaf_size,
                 uint8_t* d_root, hipStream_t stream);

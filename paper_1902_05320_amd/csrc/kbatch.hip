@@ -1,7 +1,9 @@
 // libkbatch: batch SHA-3 on gfx950 -- kernels, scheduler and the C ABI.
 //
-// keccak_batch (persistent form) is four launches on the caller's stream,
-// with no host synchronisation:
+// keccak_batch (persistent form) is up to four launches on the caller's
+// stream, with no host synchronisation.  A batch of few messages (two per
+// SIMD, no tile given) is one k_wide launch; one of up to twice as many takes
+// k_wide in k_first's place.  Else:
 //   k_first   one 64-message chunk of arrival order per wave: a chunk of
 //             one-block messages is hashed on the spot; any other chunk is
 //             deferred (its block-count keys nb = floor(L/R) + 1 counted,
@@ -9,13 +11,14 @@
 //             listed).
 //   k_second<.., 0> (plan)  one workgroup: bucket starts in descending nb,
 //             longest first; queue items of about `steps_per_item`
-//             permutations per lane; the range of the longest messages that
-//             the wide split form hashes.
+//             permutations per lane (one message per lane where there is a wave
+//             for every message); the range of the longest messages that the
+//             wide split form hashes, and which buckets take the pair form.
 //   k_second<.., 1> (tiles)  the grid fills the queue and scatters the
 //             deferred messages into bucketed order.
-//   k_second<.., 2> (hashing)  a resident grid: each SIMD's front wave takes
-//             the split range and then the longest items, the other waves the
-//             shortest ones.
+//   k_second<.., 2> (hashing)  a resident grid: each SIMD's first wave takes
+//             split items, another (the same if there are none) the longest
+//             items, the others the shortest ones.
 // Kernel boundaries order each launch's writes before the next one's reads,
 // so no workgroup waits on another or fences.  On a batch with nothing
 // deferred the last three find no work and return.
@@ -23,11 +26,12 @@
 // runs both passes without hashing, reads the bucket sizes back, and
 // launches k_plain once per non-empty bucket.
 //
-// Tree mode: k_tree hashes 256 leaves per workgroup and reduces them one
-// level; further k_tree launches reduce 256 nodes per workgroup up to eight
-// levels while more than 1024 remain; one 512-thread workgroup reduces the
-// rest to the root.  Every level is written to its own region, so no
-// workgroup reads a node another one may overwrite.
+// Tree mode: k_leaf hashes the leaves of a tree of few in the wide or the pair
+// form, k_tree those of a larger one and one level above; further k_tree
+// launches reduce 256 nodes per workgroup while more than 32 per CU remain;
+// k_tree_up takes the rest to the root, five levels a launch.  Every level that
+// a launch ends with is written to its own region, so no workgroup reads a node
+// another one may overwrite.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -780,16 +784,15 @@ __global__ __launch_bounds__(kUpThreads) void k_tree_up(uint8_t* __restrict__ no
 //           inter-workgroup synchronisation at all (the end of the kernel
 //           publishes the counts), so on a batch of one-block messages it
 //           costs what the one-thread-per-message launch costs.
-// k_second  a resident grid.  The first workgroup to arrive makes the plan
-//           for the deferred messages (bucket starts longest first, queue
-//           items, the split range) while the others wait for it; then the
-//           workgroups take tiles (queue items, and the counting-sort scatter
-//           of the deferred messages into bucketed order), wait until every
-//           tile is done, and hash: waves pop queue items (longest first)
-//           until the queue is drained.
+// k_second  three launches: one workgroup makes the plan for the deferred
+//           messages (bucket starts longest first, queue items, the split
+//           range, the forms); then workgroups take tiles (queue items, and the
+//           counting-sort scatter of the deferred messages into bucketed
+//           order); then a resident grid hashes, its waves popping queue items
+//           from both ends until the queue is drained.
 //
 // A batch of equal one-block messages is thus hashed in the first launch
-// with no sort; the second finds an empty plan and exits.
+// with no sort; the others find an empty plan and exit.
 
 __device__ __forceinline__ uint32_t load_relaxed(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2588,7 +2591,8 @@ int keccak_graph_create(int variant, const uint8_t* d_variants, const uint8_t* d
     rc = hipGetDevice(&dev) == hipSuccess ? cu_count(dev, &cus) : fail(KB_EHIP, "hipGetDevice failed");
     // up to four messages per SIMD: one node, the wide launch that the first
     // pass would be (a replay of 4096 x 64 B 22 us with the nodes that find
-    // nothing left to do, 11 without)
+    // nothing left to do; 18 without, the kernel being 10 of it and the rest, 11-19 in
+    // all from run to run, the replay of a graph)
     if (!rc && !chosen(tile) && n <= 4u * 4u * static_cast<uint64_t>(cus)) mode = KB_MODE_WIDE;
     if (!rc && mode == KB_MODE_PERSISTENT) rc = size_ws(g->ws, n, 0, stream);
     if (rc) {

@@ -5,9 +5,11 @@
 // eq. 1) and holds the little-endian 64-bit word at byte 8(x + 5y) of the
 // state, so message bytes absorb with plain little-endian dword loads.
 //
-// All 24 rounds are fully unrolled: pi (eq. 6) is pure register renaming,
-// the rho (eq. 5) rotation amounts and the iota round constants (eqs. 8-9)
-// are instruction immediates, and no memory is touched by the permutation.
+// pi (eq. 6) is pure register renaming and the rho (eq. 5) rotation amounts are
+// instruction immediates.  The one-block kernels unroll all 24 rounds, with the
+// iota round constants (eqs. 8-9) as immediates too; the kernels that loop over
+// blocks take four rounds to an iteration and read their constants with scalar
+// loads.
 // Per round the VALU work is
 //   theta column parities   20 v_bitop3 (3-input xor)
 //   theta rot-by-1 of C     10 v_alignbit

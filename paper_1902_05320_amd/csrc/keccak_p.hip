@@ -83,14 +83,15 @@ __device__ void rounds_narrow(uint32_t (&A)[25], int ir0, int nr) {
 }
 
 // n_r rounds from i_r = ir0 on 64-bit lanes: the SHA-3 path's round, in phases.
-// 2^20 states of 24 rounds: 117 us, 132 with the instructions of a round mixed
-// and one round per iteration.  (The rounds alone take 84 us at the
-// register-held rate, 420 MB 82 us at a copy's.  Going through LDS so that
-// global memory sees whole lines was the slower way, 147 against 130 at the
-// time: three waves per SIMD instead of five.)  No lambda here: one that uses
-// kRCAll makes the table visible to the loader, and every kernel of this file
-// then loads its address from the offset table each round (131 us; b = 400 116
-// against 107).
+// 2^20 states of 24 rounds: 117 us over the same states again and again (210 MB,
+// which the last-level cache holds), 131 over others each time; 132 and 137 with
+// the instructions of a round mixed and one round per iteration.  (The rounds
+// alone take 84 us at the register-held rate, 420 MB 82 us at a copy's.  Going
+// through LDS so that global memory sees whole lines was the slower way, 147
+// against 130 at the time: three waves per SIMD instead of five.)  No lambda
+// here: one that uses kRCAll makes the table visible to the loader, and every
+// kernel of this file then loads its address from the offset table each round
+// (131 us in place of 117; b = 400 116 in place of 107).
 __device__ __forceinline__ void rounds_wide(kb::Lane (&A)[25], int ir0, int nr) {
   int i = rc_index(ir0), k = 0;
 #pragma unroll 1

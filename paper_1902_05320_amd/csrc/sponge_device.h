@@ -4,8 +4,7 @@
 // words (the next one while the current one is permuted) and xored into the
 // state; nothing outside the message is touched.  Staging these blocks through
 // LDS like the final one cost 37 realignments, 10 LDS writes and 19 reads with
-// eight-way bank conflicts a block: 32768 x 4 KiB 346 us against 313, and the
-// mixed kernel held 207 registers instead of 175.
+// eight-way bank conflicts a block: 32768 x 4 KiB 346 us against 313.
 //
 // The final block of the padded message P = M || 01 || pad10*1 is staged
 // through a per-thread row of LDS:
@@ -177,8 +176,12 @@ __device__ __forceinline__ void stage_block(uint32_t* __restrict__ row, const Bl
 // interleaved A/B on one box: 4 KiB Merkle leaves 1.14 ms per 1 GiB root
 // with it against 1.23 without (three waves per SIMD against four); the
 // mixed-variant batch of lengths up to 16 KiB 2.40 ms against 2.52, although
-// the mixed kernel then holds two waves per SIMD instead of three (206 VGPRs;
-// capping it at three spills); one-block messages are level either way.
+// the mixed kernel then held two waves per SIMD instead of three (capping it at
+// three spills); one-block messages are level either way.  With the pair and
+// wide forms in them too, the hashing kernels hold 212 VGPRs (mixed), 189 and
+// 185 (SHA3-224 and 256), 202 and 181 (SHAKE128 and 256), two waves per SIMD,
+// and 164 and 146 (SHA3-384 and 512), three; without the prefetch 175 (mixed,
+// two waves) and 132-153 (three).
 // The chain of the longest message bounds a batch of uneven lengths, so the
 // latency of each block matters more than the occupancy.
 template <int V>

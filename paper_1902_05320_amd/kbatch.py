@@ -243,7 +243,8 @@ def keccak_batch(variant, data: torch.Tensor, offsets: torch.Tensor, lengths: to
                  out: torch.Tensor | None = None, stream=None, mode="persistent",
                  tile: Tile | None = None, check_bounds: bool = True) -> torch.Tensor:
     """SHA-3 digests of every (offset, length) slice of `data`; returns
-    uint8[n, D] on the device.  `mode` is persistent, plain, per_bucket, split or wide."""
+    uint8[n, D] on the device.  `mode` is persistent, plain, per_bucket, split,
+    wide or pair."""
     _require_gpu()
     lib = load_library()
     v = variant_id(variant)
@@ -346,7 +347,7 @@ def keccak_batch_xof(security: int, data: torch.Tensor, offsets: torch.Tensor,
                      mode: str = "persistent") -> torch.Tensor:
     """SHAKE128/256 of every slice, out_len bytes each; returns uint8[n, out_len].
 
-    mode: "persistent" (default), "plain", "per_bucket", "split" or "wide"."""
+    mode: "persistent" (default), "plain", "per_bucket", "split", "wide" or "pair"."""
     _require_gpu()
     lib = load_library()
     if security not in (128, 256):
@@ -420,7 +421,8 @@ def autotune(variant, data: torch.Tensor, offsets: torch.Tensor, lengths: torch.
              variants: torch.Tensor | None = None, reps: int = 3, stream=None,
              cache: str | None = None):
     """Pick the persistent-form tile for this batch (every candidate checked
-    bit for bit against the plain form first).  variant=-1 with `variants`
+    bit for bit against the plain form first; a Tile of zeros is the library's own
+    choice, the same as none).  variant=-1 with `variants`
     tunes the mixed form.  With `cache`, the result is merged into that JSON
     tune cache under this device's key.  Returns (Tile, ms, rejected)."""
     _require_gpu()
