@@ -210,8 +210,8 @@ int merkle_root(int variant, const uint8_t* d_data, uint64_t total_len, uint64_t
  * steps_per_item {1, 2, 4, 8, 16, 32}; then threads per state by
  * block-count class (the wide split tail from each class present upward, or
  * one lane everywhere); then steps per queue item for each class present
- * {1, 4, 16}; then no tile at all (a zero *best if that is the fastest: the
- * library's own choice, which for a small batch is one wide launch).  Every candidate's digests are first compared with the plain
+ * {1, 4, 16}; then, for a batch small enough for the wide form (KB_MODE_PERSISTENT),
+ * no tile at all (a zero *best if that is the fastest).  Every candidate's digests are first compared with the plain
  * form's bit for bit (a candidate that differs is discarded and counted in
  * *rejected); the verified ones are timed with HIP events (median of `reps`
  * runs).  The fastest goes to *best and its time to *best_ms.  Arguments as

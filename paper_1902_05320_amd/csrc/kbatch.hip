@@ -1815,12 +1815,13 @@ int launch_split(const Batch& b, const uint32_t* order, uint64_t first, uint64_t
 
 template <int V>
 int launch_wide(const Batch& b, const uint32_t* order, uint64_t first, uint64_t count,
-                hipStream_t s, int kind = KB_KERNEL_WIDE) {
+                hipStream_t s, int kind = KB_KERNEL_WIDE, int cus = 0) {
   if (!count) return KB_OK;
-  int dev = 0, cus = 0;
-  KB_HIP(hipGetDevice(&dev));
-  int rc = cu_count(dev, &cus);
-  if (rc) return rc;
+  if (!cus) {
+    int dev = 0;
+    KB_HIP(hipGetDevice(&dev));
+    if (int rc = cu_count(dev, &cus)) return rc;
+  }
   // one message per wave up to 32 waves per CU (a wave holds 41 registers and no
   // LDS memory); beyond that waves loop.  16384 x 4 KiB SHA3-256 692 us, 718 with
   // 16 waves per CU; 8192 of up to 2000 bytes 66 and 80.
@@ -1879,6 +1880,12 @@ int resident_grid(const void* kernel, const kb_tile* tile, int dev, int cus, uin
   *grid = static_cast<uint32_t>(per_cu * cus);
   return KB_OK;
 }
+
+// Most messages that a batch with no tile hashes in its wide first launch, and
+// most for which that launch is the only one (four and two per SIMD; the
+// measurements stand where they are used).
+constexpr uint64_t wide_first_max(int cus) { return 4u * 4u * static_cast<uint64_t>(cus); }
+constexpr uint64_t wide_only_max(int cus) { return kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus); }
 
 // The second pass for a tile's staging form: blocks loaded when absorbed
 // (KB_STAGING_DIRECT, SHA-3 variants) or the next block prefetched into
@@ -1946,9 +1953,9 @@ int run_two_pass(const Batch& b, Workspace& w, int mode, const kb_tile* tile, hi
   // 4096 11.6 where a thread per message takes 13-15; at 8192 x 64 B it is the
   // slower one (17.6 against 13.6).  The launches after it find nothing to do;
   // they stay because callers count on them (the timing brackets of a call).
-  const bool wide_first = !per_bucket && !tile && !n_dev && b.n <= 4u * 4u * static_cast<uint64_t>(cus);
+  const bool wide_first = !per_bucket && !tile && !n_dev && b.n <= wide_first_max(cus);
   if (wide_first) {
-    if ((rc = launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS))) return rc;
+    if ((rc = launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS, cus))) return rc;
   } else {
     TimedLaunch tl(s, KB_KERNEL_FIRST_PASS);
     hipLaunchKernelGGL(k_first<V>, dim3(grid1), dim3(kBlock), 0, s, a);
@@ -2005,9 +2012,8 @@ int run_batch(const Batch& b, int mode, const kb_tile* tile, hipStream_t s, Work
   int dev = 0, cus = 0;
   KB_HIP(hipGetDevice(&dev));
   if (int rc = cu_count(dev, &cus)) return rc;
-  if (mode == KB_MODE_PERSISTENT && !tile && !n_dev &&
-      b.n <= kSplitItemsPerSimd * 4u * static_cast<uint64_t>(cus))
-    return launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS);
+  if (mode == KB_MODE_PERSISTENT && !tile && !n_dev && b.n <= wide_only_max(cus))
+    return launch_wide<V>(b, nullptr, 0, b.n, s, KB_KERNEL_FIRST_PASS, cus);
   if (b.n >= 0xFFFFFFFFull) return launch_plain<V>(b, nullptr, 0, b.n, s);  // 32-bit order[]
   Workspace* w = own;
   int rc = own ? KB_OK : get_ws(s, b.n, 0, &w);
@@ -2558,10 +2564,13 @@ int keccak_autotune(int variant, const uint8_t* d_variants, const uint8_t* d_dat
       if ((rc = consider(t))) break;
     }
   }
-  // 5. no tile: a small batch then runs in one wide launch, which no tile asks
-  // for (300 messages of 200 bytes: 10 us a call, 43 with the best tile), and a
-  // tile stored for it would displace that
-  if (!rc) rc = consider(kb_tile{});
+  // 5. no tile: a small batch then runs in the wide form, which no tile asks for
+  // (300 messages of 200 bytes: 10 us a call, 43 with the best tile), and a tile
+  // stored for it would displace that.  (Above that size no tile is the first
+  // candidate again.)
+  int dev = 0, cus = 0;
+  if (!rc) rc = hipGetDevice(&dev) == hipSuccess ? cu_count(dev, &cus) : fail(KB_EHIP, "hipGetDevice failed");
+  if (!rc && n <= wide_first_max(cus)) rc = consider(kb_tile{});
   cleanup();
   if (rc) return rc;
   *best = cur;
@@ -2593,7 +2602,7 @@ int keccak_graph_create(int variant, const uint8_t* d_variants, const uint8_t* d
     // pass would be (a replay of 4096 x 64 B 22 us with the nodes that find
     // nothing left to do; 18 without, the kernel being 10 of it and the rest, 11-19 in
     // all from run to run, the replay of a graph)
-    if (!rc && !chosen(tile) && n <= 4u * 4u * static_cast<uint64_t>(cus)) mode = KB_MODE_WIDE;
+    if (!rc && !chosen(tile) && n <= wide_first_max(cus)) mode = KB_MODE_WIDE;
     if (!rc && mode == KB_MODE_PERSISTENT) rc = size_ws(g->ws, n, 0, stream);
     if (rc) {
       free_ws(g->ws);
